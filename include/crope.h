@@ -213,11 +213,13 @@ int chunk_attention_planned(
  * scratch for the partial results of a split key range is a buffer of
  * CROPE_STATIC_SCRATCH_BYTES built into the library, one copy per GPU, held from the moment the
  * library is loaded on that GPU until the process ends.  The call allocates and frees nothing.
- * Same arguments, same kernels, same work division and bit-identical results as
- * chunk_attention, minus workspace / workspace_bytes.
+ * Same arguments and same kernels as chunk_attention, minus workspace / workspace_bytes; same work
+ * division and bit-identical results wherever chunk_attention's scratch fits the buffer.
  *   - CROPE_EWORKSPACE, before anything is launched, if the problem would need more scratch
- *     than the buffer holds (chunk_attention_workspace_bytes(...) > CROPE_STATIC_SCRATCH_BYTES);
- *     the 40-head 585-query x 32760-key rank share needs 58 MiB.
+ *     than the buffer holds (chunk_attention_workspace_bytes(...) > CROPE_STATIC_SCRATCH_BYTES;
+ *     300 queries x 64 heads x 60000 keys), except for sizes that fitted it under the library's first
+ *     work division: those run with the best division that fits (a 1280x720 chunk: 10800 queries x
+ *     12 heads, unsplit).  The 40-head 585-query x 32760-key rank share needs 23 MiB.
  *   - The first call on a GPU looks the buffer's device address up (a runtime query, no
  *     allocation) and keeps it for later calls; call with that GPU current.  Make that first
  *     call outside any graph capture.

@@ -354,22 +354,24 @@ int chunk_attention_static(const void* q, crope_strides q_strides, int32_t n_q, 
                            float scale, void* out, crope_strides out_strides, float* lse_or_null,
                            void* stream) {
   // the size check comes first: a problem too large for the static buffer touches no GPU state
+  crope_attention_plan plan = {0, 0};
   if (n_q > 0 && n_heads > 0 && segs && n_segs >= 1 && n_segs <= crope::kMaxSegments) {
     int64_t n_keys = 0;
     for (int i = 0; i < n_segs; ++i) n_keys += segs[i].len > 0 ? segs[i].len : 0;
     if (n_keys > 0 && n_keys <= ((int64_t)1 << 30)) {
-      const size_t need = crope::attention_workspace_bytes(n_q, n_heads, n_keys, crope::AttnPlan{0, 0});
-      if (need > kStaticScratchBytes)
+      crope::AttnPlan p;
+      if (!crope::attention_static_plan(n_q, n_heads, n_keys, &p))
         return fail(CROPE_EWORKSPACE,
                     "chunk_attention_static: this problem needs %zu bytes of scratch, the built-in "
                     "buffer holds %zu; use chunk_attention with a caller-provided workspace",
-                    need, kStaticScratchBytes);
+                    crope::attention_workspace_bytes(n_q, n_heads, n_keys, crope::AttnPlan{0, 0}), kStaticScratchBytes);
+      plan = crope_attention_plan{p.waves, p.splits};
     }
   }
   void* ws = nullptr;
   if (int rc = static_scratch(&ws)) return rc;
   return attention_impl(q, q_strides, n_q, n_heads, k_cache, v_cache, cache_strides, cache_capacity_tokens,
-                        segs, n_segs, scale, nullptr, false, nullptr, out, out_strides, lse_or_null, ws,
+                        segs, n_segs, scale, nullptr, false, &plan, out, out_strides, lse_or_null, ws,
                         kStaticScratchBytes, stream);
 }
 

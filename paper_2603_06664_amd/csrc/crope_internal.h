@@ -85,6 +85,9 @@ int rope_max_heads();
 // 32-query units per work-group (4 or 8) and key splits (1..16); 0 = let the library choose
 struct AttnPlan { int waves; int splits; };
 AttnPlan attention_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
+// the plan of chunk_attention_static: attention_plan's, or where that one's partial results exceed the built-in
+// buffer the best one that fits it; false where such a size has always been refused
+bool attention_static_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan* plan);
 hipError_t launch_attention(const AttnArgs& a, AttnPlan want, hipStream_t st);
 size_t attention_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
 hipError_t launch_project(const ProjArgs& a, hipStream_t st);
