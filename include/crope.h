@@ -256,6 +256,10 @@ int chunk_attention_limited(
  * row-wide norm about 512 bytes per token and head). */
 size_t crope_qkv_project_workspace_bytes(int32_t n_tokens, int32_t n_heads, int32_t norm_group);
 
+/* Token rows of one work-group's tile that crope_qkv_project_norm_rotate_append takes for a size (192 or
+ * 256; results do not depend on it).  0 for sizes that are not positive. */
+int32_t crope_qkv_project_tile_tokens(int32_t n_tokens, int32_t n_heads, int32_t c_in);
+
 /* Local QKV projection fused with crope_qk_norm_rotate_append (Algorithm 3 steps 1, 2, 3 and
  * 5 in one call; the projection + RoPE operator fusion of Section 3.4.1 item 3).
  *

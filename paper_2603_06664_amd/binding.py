@@ -119,6 +119,8 @@ def _load():
         _Strides, vp, vp]
     lib.crope_qkv_project_workspace_bytes.restype = ctypes.c_size_t
     lib.crope_qkv_project_workspace_bytes.argtypes = [i32, i32, i32]
+    lib.crope_qkv_project_tile_tokens.restype = i32
+    lib.crope_qkv_project_tile_tokens.argtypes = [i32, i32, i32]
     lib.crope_qkv_project_norm_rotate_append.restype = ctypes.c_int
     lib.crope_qkv_project_norm_rotate_append.argtypes = [
         ctypes.POINTER(_Desc), vp, vp, i64, vp, vp, i32, vp, vp, f32, i32, i32, i32, i32, i32, i32,
@@ -306,6 +308,10 @@ def chunk_attention_limited(q, n_q: int, n_heads: int, k_cache, v_cache, cache_c
 
 def crope_qkv_project_workspace_bytes(n_tokens: int, n_heads: int, norm_group: int) -> int:
     return int(_load().crope_qkv_project_workspace_bytes(n_tokens, n_heads, norm_group))
+
+
+def crope_qkv_project_tile_tokens(n_tokens: int, n_heads: int, c_in: int) -> int:
+    return int(_load().crope_qkv_project_tile_tokens(n_tokens, n_heads, c_in))
 
 
 def crope_qkv_project_norm_rotate_append(desc: TableDesc, d_table, x, w_qkv, bias, c_in: int, gain_q,

@@ -390,6 +390,11 @@ size_t crope_qkv_project_workspace_bytes(int32_t n_tokens, int32_t n_heads, int3
   return crope::project_workspace_bytes(n_tokens, n_heads, norm_group == crope::kHeadDim);
 }
 
+int32_t crope_qkv_project_tile_tokens(int32_t n_tokens, int32_t n_heads, int32_t c_in) {
+  if (n_tokens <= 0 || n_heads <= 0 || c_in <= 0) return 0;
+  return crope::project_tile_tokens(n_tokens, n_heads, c_in);
+}
+
 int crope_qkv_project_norm_rotate_append(
     const crope_table_desc* desc, const float* d_table, const void* x, int64_t x_token_stride,
     const void* w_qkv, const float* bias_or_null, int32_t c_in, const float* gain_q,

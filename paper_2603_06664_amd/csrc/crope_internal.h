@@ -90,6 +90,7 @@ AttnPlan attention_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
 bool attention_static_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan* plan);
 hipError_t launch_attention(const AttnArgs& a, AttnPlan want, hipStream_t st);
 size_t attention_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
+int project_tile_tokens(int n_tokens, int n_heads, int c_in);   // width of launch_project's tiles
 hipError_t launch_project(const ProjArgs& a, hipStream_t st);
 size_t project_workspace_bytes(int n_tokens, int n_heads, bool per_head_norm);
 

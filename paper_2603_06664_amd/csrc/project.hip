@@ -536,10 +536,10 @@ size_t project_workspace_bytes(int n_tokens, int n_heads, bool per_head_norm) {
 }
 
 template <class S>
-static ProjTiles make_tiles(const ProjArgs& a) {
+static ProjTiles make_tiles(int n_tokens, int n_heads) {
   ProjTiles pt;
-  pt.ch_tiles = 3 * a.n_heads;
-  pt.tok_tiles = (a.n_tokens + S::kTileTok - 1) / S::kTileTok;
+  pt.ch_tiles = 3 * n_heads;
+  pt.tok_tiles = (n_tokens + S::kTileTok - 1) / S::kTileTok;
   pt.total = pt.ch_tiles * pt.tok_tiles;
   pt.per_xcd = (pt.total + kXcds - 1) / kXcds;
   pt.wgs_per_xcd = pt.per_xcd < 32 ? pt.per_xcd : 32;
@@ -548,7 +548,8 @@ static ProjTiles make_tiles(const ProjArgs& a) {
 static int rounds(const ProjTiles& pt) { return (pt.per_xcd + pt.wgs_per_xcd - 1) / pt.wgs_per_xcd; }
 
 template <class S>
-static void launch_tiles(const ProjArgs& a, const ProjTiles& pt, hipStream_t st) {
+static void launch_tiles(const ProjArgs& a, hipStream_t st) {
+  const ProjTiles pt = make_tiles<S>(a.n_tokens, a.n_heads);
   const dim3 grid(pt.wgs_per_xcd * kXcds), block(S::kThreads);
   if (a.per_head_norm) hipLaunchKernelGGL((qkv_project_kernel<S, true>), grid, block, 0, st, a, pt);
   else hipLaunchKernelGGL((qkv_project_kernel<S, false>), grid, block, 0, st, a, pt);
@@ -558,19 +559,31 @@ static void launch_tiles(const ProjArgs& a, const ProjTiles& pt, hipStream_t st)
 // heads: 336 us, 380 us in tiles of 192).  192: one wave per SIMD, for calls whose rounds of 256-wide
 // tiles over the 256 CUs end nearly empty or whose last tile is mostly padding.  A round of 192-wide
 // tiles takes 0.85 to 0.89 of a round of 256-wide ones where both take two rounds (585 rows x 120 channel
-// tiles: 108 against 122 us; 4680 x 15: 104 / 123; 1320 x 48 in half-filled rounds: 51 / 58), so it is
-// taken where its rounds at that price are cheaper.  Tiles of 128 were never the fastest (122, 122, 61 us).
+// tiles: 108 against 122 us; 4680 x 15: 104 / 123; 1320 x 48 in half-filled rounds: 51 / 58) and 0.84 to
+// 0.98 where both take one (us, 192 / 256: 384 rows x 120 channel tiles, c_in 5120: 57 / 67; 600 x 36, 1536:
+// 29.4 / 30.7; 600 x 24, 1024: 17.1 / 17.4), so it is taken where its rounds at that price are cheaper.  At
+// short reductions the epilogue, which 8 waves work off faster, is most of a tile, and 256 is never the
+// slower one (us, 192 / 256: 600 x 6, c_in 256: 11.7 / 11.2; 600 x 9, 384: 12.4 / 12.2; equal at 512 and 640).
+// Tiles of 128 were never the fastest (122, 122, 61 us where the first three calls take 108, 104, 51).
 using Wide = Shape<4, 2>;
 using Mid = Shape<2, 3>;
 constexpr double kMidCost = 0.88;
+constexpr int kShortReduction = 512;
+
+template <class S>
+static int rounds(int n_tokens, int n_heads) { return rounds(make_tiles<S>(n_tokens, n_heads)); }
+
+int project_tile_tokens(int n_tokens, int n_heads, int c_in) {
+  const double mid_cost = c_in <= kShortReduction ? 1.0 : kMidCost;
+  return rounds<Wide>(n_tokens, n_heads) <= rounds<Mid>(n_tokens, n_heads) * mid_cost ? Wide::kTileTok : Mid::kTileTok;
+}
 
 hipError_t launch_project(const ProjArgs& a_in, hipStream_t st) {
   ProjArgs a = a_in;
   if (!a.per_head_norm)
     a.resid = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(a.sumsq) + sumsq_bytes(a.n_tokens, a.n_heads));
-  const ProjTiles wide = make_tiles<Wide>(a), mid = make_tiles<Mid>(a);
-  if (rounds(wide) <= rounds(mid) * kMidCost) launch_tiles<Wide>(a, wide, st);
-  else launch_tiles<Mid>(a, mid, st);
+  if (project_tile_tokens(a.n_tokens, a.n_heads, a.c_in) == Wide::kTileTok) launch_tiles<Wide>(a, st);
+  else launch_tiles<Mid>(a, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.per_head_norm) return e;
   hipLaunchKernelGGL(scale_rows_kernel, dim3(2, (a.n_tokens + kScaleWaves - 1) / kScaleWaves),

@@ -62,8 +62,8 @@ def test_small_every_element(P, cfg, c_in, per_head):
     _check(cfg, got, ref, per_head)
 
 
-# 40 heads are 120 channel tiles on 256 CUs, so the token count decides the tile width: 129, 385 and 512
-# rows take tiles of 256 tokens, 257, 384 (both widths' edge) and 540 tiles of 192; reduction lengths as above.
+# 40 heads are 120 channel tiles on 256 CUs: one or two rounds of either tile width, ragged in both; short
+# reductions, as above, take tiles of 256 tokens (checked in test_projection_widths.py, with those of 192).
 @pytest.mark.parametrize("n,c_in", [(129, 320), (257, 64), (257, 448), (384, 128), (385, 320), (512, 192), (540, 192)])
 @pytest.mark.parametrize("per_head", [False, True], ids=["normHD", "normD"])
 def test_tile_widths(P, n, c_in, per_head):
