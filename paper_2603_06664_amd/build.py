@@ -31,7 +31,7 @@ def _stale() -> bool:
         return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(CEILINGS_LIB))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h"))] + \
-           [os.path.join(HERE, "..", "include", "crope.h")]
+           [os.path.join(HERE, "..", "include", "crope.h"), os.path.abspath(__file__)]   # the flags are in here
     return any(os.path.getmtime(d) > t for d in deps)
 
 
