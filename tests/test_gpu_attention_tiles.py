@@ -80,3 +80,13 @@ def test_second_run(P, n_keys, folded):
     # limits below, inside and beyond the keys that jump
     limits = np.minimum(n_keys, 1 + (np.arange(300) * 7) % (n_keys + 20))
     _case(P, 0, 0, 300, n_keys, folded, limits=limits, jump_at=70)
+
+
+@pytest.mark.parametrize("H", [1, 5, 8, 12])
+def test_limited_work_order(P, H):
+    """Every (head, query tile) is worked off once, whatever the head count leaves over on the 8 XCDs; limits
+    that rise with the query, fall with it, and neither."""
+    n = 600
+    i = np.arange(n)
+    for limits in (1 + i, n - i, 1 + (i * 37) % n):
+        _case(P, 0, 0, n, n, True, limits=limits, H=H)
