@@ -4,7 +4,8 @@ Those MFMAs are inline assembly, which the compiler's hazard pass does not look 
 guarantees for every other MFMA is checked here on the assembly of the kernels (gfx950 needs no GPU to
 compile for): two wait states between a vector instruction that writes one of the MFMA's operands and the
 MFMA, and, after the MFMA, at least the 18 wait states of the longest MFMA before anything but another
-MFMA touches its result."""
+MFMA touches its result.  The copies from memory to LDS are inline assembly too: one wait state behind a
+scalar write of M0, five behind a vector instruction that writes one of their scalar operands."""
 import os
 import re
 import subprocess
@@ -15,6 +16,8 @@ from paper_2603_06664_amd import build
 
 OPERAND_WAITS = 2
 RESULT_WAITS = 18
+M0_WAITS = 1
+SCALAR_WAITS = 5
 
 _REG = re.compile(r"\b([av])(?:\[(\d+):(\d+)\]|(\d+))(?![\w\]])")
 
@@ -24,6 +27,16 @@ def _regs(text):
     for kind, lo, hi, one in _REG.findall(text):
         first, last = (int(one), int(one)) if one else (int(lo), int(hi))
         out.update((kind, i) for i in range(first, last + 1))
+    return out
+
+
+_SREG = re.compile(r"\bs(?:\[(\d+):(\d+)\]|(\d+))(?![\w\]])")
+
+
+def _scalar_regs(text):
+    out = set()
+    for lo, hi, one in _SREG.findall(text):
+        out.update(range(int(lo or one), int(hi or one) + 1))
     return out
 
 
@@ -42,11 +55,15 @@ class Ins:
                 cur += ch
         ops.append(cur)
         self.mfma = self.op.startswith("v_mfma")
+        self.copy = self.op.startswith("global_load_lds") or (self.op.startswith("buffer_load") and rest.endswith("lds"))
+        self.first = ops[0].strip()
+        self.scalar = _scalar_regs(rest) if self.copy else set()
+        self.vector_writes_scalar = _scalar_regs(self.first) if self.op.startswith("v_") else set()
         self.regs = _regs(rest)
         n_dst = 0 if not self.op.startswith("v_") or self.op.startswith("v_cmp") else 2 if "swap" in self.op else 1
         self.writes = _regs(",".join(ops[:n_dst]))
         # a copy that its inline-assembly branch may skip counts for nothing
-        self.waits = int(rest, 0) + 1 if self.op == "s_nop" else 0 if in_asm and self.op.startswith("global_load_lds") else 1
+        self.waits = int(rest, 0) + 1 if self.op == "s_nop" else 0 if in_asm and self.copy else 1
         self.target = rest.strip() if self.op.startswith(("s_cbranch", "s_branch")) else None
 
 
@@ -115,6 +132,11 @@ def faults(asm):
     for name, code in kernels.items():
         pred, succ = _edges(code)
         for i, x in enumerate(code):
+            if isinstance(x, Ins) and x.copy and x.in_asm:
+                w = _walk(code, pred, i, M0_WAITS, lambda y: y.first == "m0") or \
+                    _walk(code, pred, i, SCALAR_WAITS, lambda y: bool(y.vector_writes_scalar & x.scalar))
+                if w:
+                    out.append("%s: '%s' too close before '%s'" % (name, w, x.text))
             if not (isinstance(x, Ins) and x.mfma and x.in_asm):
                 continue
             w = _walk(code, pred, i, OPERAND_WAITS, lambda y: not y.mfma and bool(y.writes & x.regs))
@@ -150,9 +172,19 @@ def test_planted_faults_are_seen():
     assert len(faults(text % (".LBB0_1:", far + "\nv_mov_b32_e32 v4, v8\ns_cbranch_scc1 .LBB0_1"))[0]) == 1
 
 
+def test_planted_copy_faults_are_seen():
+    text = "_Zk:\nv_mfma_f32_32x32x16_bf16 a[0:15], v[0:3], v[4:7], a[0:15]\n%s\n;;#ASMSTART\n%s\n;;#ASMEND\ns_endpgm\n.Lfunc_end0:\n"
+    copy = "s_add_u32 s7, s7, s8\nbuffer_load_dwordx4 v3, s[12:15], s7 offen lds"
+    assert not faults(text % ("v_readfirstlane_b32 s14, v0\ns_nop 3\ns_mov_b32 m0, s3", copy))[0]
+    assert len(faults(text % ("s_mov_b32 m0, s3", "buffer_load_dwordx4 v3, s[12:15], s7 offen lds"))[0]) == 1
+    assert len(faults(text % ("v_readlane_b32 s14, v0, 3\ns_nop 2", copy))[0]) == 1
+    assert len(faults(text % ("v_readfirstlane_b32 s7, v0\ns_mov_b32 m0, s3", copy))[0]) == 1
+
+
 def test_o_mfmas_have_their_wait_states(attention_asm):
     found, kernels = faults(attention_asm)
     assert len(kernels) == 8   # 2 work-group shapes x limited or not x folded or not
     for code in kernels.values():
         assert sum(isinstance(x, Ins) and x.mfma and x.in_asm for x in code) >= 32
+        assert sum(isinstance(x, Ins) and x.copy and x.in_asm for x in code) >= 16
     assert not found, "\n".join(found[:20])
