@@ -1,5 +1,6 @@
 """Build libcrope.so (HIP, gfx950) in-tree with hipcc.  No torch extension machinery: the
-library is a plain C-ABI shared object loaded with ctypes."""
+library is a plain C-ABI shared object loaded with ctypes; only _fastcall.so, which hands torch tensors
+to it, is compiled against torch's headers."""
 from __future__ import annotations
 
 import os
@@ -17,6 +18,9 @@ CEILINGS_SOURCE = "ceilings.hip"
 # attention kernel's design come from it
 ISSUE_BENCH = os.path.join(HERE, "issue_bench")
 ISSUE_BENCH_SOURCE = "issue_bench.hip"
+# argument marshalling of the per-chunk calls (a Python extension module; host code only)
+FASTCALL = os.path.join(HERE, "_fastcall.so")
+FASTCALL_SOURCE = "fastcall.cpp"
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
@@ -27,12 +31,24 @@ SOURCE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(CEILINGS_LIB):
+    built = (LIB, CEILINGS_LIB, FASTCALL)
+    if not all(os.path.exists(f) for f in built):
         return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(CEILINGS_LIB))
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h"))] + \
+    t = min(os.path.getmtime(f) for f in built)
+    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h", ".cpp"))] + \
            [os.path.join(HERE, "..", "include", "crope.h"), os.path.abspath(__file__)]   # the flags are in here
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def _fastcall_command() -> list:
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            *[f for d in cpp_extension.include_paths() for f in ("-isystem", d)],
+            "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, FASTCALL_SOURCE), "-o", FASTCALL + ".tmp",
+            *["-L" + d for d in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
 def build(force: bool = False, verbose: bool = False) -> str:
@@ -45,6 +61,8 @@ def build(force: bool = False, verbose: bool = False) -> str:
     cmd = ["hipcc", *[f for f in FLAGS if f not in ("-fPIC", "-fvisibility=hidden")],
            os.path.join(CSRC, ISSUE_BENCH_SOURCE), "-o", ISSUE_BENCH]
     procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    cmd = _fastcall_command()
+    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
         cmd = ["hipcc", *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
@@ -54,7 +72,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError("hipcc failed: %s\n%s" % (" ".join(cmd), out))
+            raise RuntimeError("%s failed: %s\n%s" % (cmd[0], " ".join(cmd), out))
         if verbose and out.strip():
             print(out)
     # link against libamdhip64 by soname only (no rpath): inside a torch process the
@@ -63,6 +81,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
     os.replace(CEILINGS_LIB + ".tmp", CEILINGS_LIB)
+    os.replace(FASTCALL + ".tmp", FASTCALL)
     return LIB
 
 
