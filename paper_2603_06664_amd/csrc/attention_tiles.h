@@ -24,7 +24,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
-constexpr int kUnitKeys = 64;            // granularity of a key split
 constexpr int kRowBytes = kHeadDim * 2;  // 256 B per key row in LDS (swizzled, unpadded)
 constexpr int kBlkBytes = 32 * kRowBytes;   // a block of 32 keys
 constexpr int kWaves = 4;                // waves per work-group, one per SIMD
