@@ -38,6 +38,7 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
 #define LDS_ADDR(p) ((uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)(p)))
 
@@ -80,8 +81,8 @@ struct Shape {
 
 template <class S>
 struct TileLoader {   // scalars only
-  const uint8_t* a_base;   // W + first channel row of the tile (wave-uniform)
-  const uint8_t* b_base;   // x + first token row of the tile (wave-uniform)
+  u32x4_t a_buf;           // W from the tile's first channel row on
+  u32x4_t b_buf;           // x from the tile's first token row on
   // per-lane byte offsets of the lane's chunk for load instruction t: row 8*wave + lane/8 + 8*waves*t
   uint32_t a_off[S::kACopies];
   uint32_t b_off[2 * S::TT];
@@ -95,24 +96,33 @@ struct TileLoader {   // scalars only
 // The copy is inline assembly, not the compiler's builtin: while a builtin copy is in flight
 // the compiler turns every counted wait on an LDS read into a wait for all of them.  LDS
 // address of lane i's 16 bytes: M0 + 16*i; M0 is an input operand bound to that register, the
-// s_nop covers the wait state after its write and the five after a v_readlane that restores a
-// spilled base (the compiler does not insert those for instructions it cannot see).
-__device__ __forceinline__ void copy16(const uint8_t* base /* wave-uniform */, uint32_t lane_off,
-                                       uint8_t* lds_dst /* wave-uniform */) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane(LDS_ADDR(lds_dst));
-  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(lane_off), "s"(base), "{m0}"(m0) : "memory");
+// s_nop covers the wait state after its write.  Base and step are scalar (a buffer and its scalar offset), so that a
+// copy costs no vector instruction and two scalar ones (585 rows x 40 heads 106.9 -> 101.7 us, 600 x 8 17.7 -> 16.3;
+// with 64-bit bases and LDS addresses taken from pointers it were eight).  A vector instruction that wrote one of the
+// buffer's words would need five wait states that the compiler does not insert here: the words are formed ahead
+// of the loop, and the tests check the assembly.
+__device__ __forceinline__ void copy16(u32x4_t buf, uint32_t lane_off, uint32_t k_off /* wave-uniform */,
+                                       uint32_t lds_dst /* wave-uniform */) {
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_dst);
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(lane_off), "s"(buf), "s"(k_off), "{m0}"(m0) : "memory");
+}
+// 2^32 - 1 bytes from `base` on: offsets stay below (255 rows of at most 2^23 bytes, and 2^21 bytes of reduction)
+__device__ __forceinline__ u32x4_t raw_buffer(const uint8_t* base /* wave-uniform */) {
+  const uint64_t a = (uint64_t)base;
+  return u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)), 0xffffffffu, 0x00020000u};
 }
 
 // copy i of reduction step kt: the W tile first, then the x tile behind it in the stage
 template <class S>
-__device__ __forceinline__ void load_copy(const TileLoader<S>& L, int kt, uint8_t* stage, int i) {
-  const int64_t k_off = (int64_t)kt * kRowB;
-  if (i < S::kACopies) copy16(L.a_base + k_off, L.a_off[i], stage + L.lds_off + i * (S::kWaves * 1024));
-  else copy16(L.b_base + k_off, L.b_off[i - S::kACopies], stage + L.lds_off + i * (S::kWaves * 1024));
+__device__ __forceinline__ void load_copy(const TileLoader<S>& L, int kt, uint32_t stage, int i) {
+  const uint32_t k_off = (uint32_t)kt * kRowB;
+  if (i < S::kACopies) copy16(L.a_buf, L.a_off[i], k_off, stage + L.lds_off + i * (S::kWaves * 1024));
+  else copy16(L.b_buf, L.b_off[i - S::kACopies], k_off, stage + L.lds_off + i * (S::kWaves * 1024));
 }
 template <class S>
-__device__ __forceinline__ void load_stage(const TileLoader<S>& L, int kt, uint8_t* stage) {
+__device__ __forceinline__ void load_stage(const TileLoader<S>& L, int kt, uint32_t stage) {
 #pragma unroll
   for (int i = 0; i < S::kCopies; ++i) load_copy<S>(L, kt, stage, i);
 }
@@ -152,7 +162,7 @@ __device__ __forceinline__ void wait_and_barrier() {
 // the step's barrier behind its first MFMA and reads the next stage's first fragments.
 template <class S, bool STEADY>   // STEADY: kt + 2 < n_kt is known, no conditions in the step
 __device__ __forceinline__ void step(f32x16_t (&acc)[2][S::TT], Frags<S::TT>& f0, Frags<S::TT>& f1,
-                                     const TileLoader<S>& L, int kt, int n_kt, const uint8_t* rd, uint8_t* ld, const uint8_t* nx, int a_off0,
+                                     const TileLoader<S>& L, int kt, int n_kt, const uint8_t* rd, uint32_t ld, const uint8_t* nx, int a_off0,
                                      int b_off0) {
   constexpr int TT = S::TT, kMfmas = 2 * TT, kCopies = S::kCopies;
   const bool prefetch = STEADY || kt + 2 < n_kt;
@@ -210,6 +220,7 @@ void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
   uint8_t* const lds0 = lds;
   uint8_t* const lds1 = lds + kStage;
   uint8_t* const lds2 = lds + 2 * kStage;
+  const uint32_t dst0 = LDS_ADDR(lds), dst1 = dst0 + kStage, dst2 = dst1 + kStage;   // the same, for the copies
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -234,8 +245,8 @@ void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
     const uint32_t chunk_bytes = (uint32_t)((l_slot ^ f) * 16);
     const int row = 8 * wave + l_row;
     const int64_t a_row_bytes = (int64_t)a.c_in * 2, b_row_bytes = a.x_tok * 2;
-    L.a_base = reinterpret_cast<const uint8_t*>(a.w) + (int64_t)ch_tile * kTileCh * a_row_bytes;
-    L.b_base = reinterpret_cast<const uint8_t*>(a.x) + (int64_t)tok0 * b_row_bytes;
+    L.a_buf = raw_buffer(reinterpret_cast<const uint8_t*>(a.w) + (int64_t)ch_tile * kTileCh * a_row_bytes);
+    L.b_buf = raw_buffer(reinterpret_cast<const uint8_t*>(a.x) + (int64_t)tok0 * b_row_bytes);
     const int last = a.n_tokens - 1 - tok0;   // >= 0
 #pragma unroll
     for (int t = 0; t < S::kACopies; ++t) L.a_off[t] = (uint32_t)((row + 8 * kWaves * t) * a_row_bytes) + chunk_bytes;
@@ -258,9 +269,9 @@ void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
 
   const int n_kt = a.c_in / kStepK;
   Frags<TT> f0, f1;
-  load_stage<S>(L, 0, lds0);
+  load_stage<S>(L, 0, dst0);
   if (n_kt > 1) {
-    load_stage<S>(L, 1, lds1);
+    load_stage<S>(L, 1, dst1);
     wait_and_barrier<kCopies>();
   } else {
     wait_and_barrier<0>();
@@ -272,16 +283,16 @@ void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
   __builtin_amdgcn_s_waitcnt(0xC07F);
   int kt = 0;
   for (; kt + 4 < n_kt; kt += 3) {   // steady state: every step prefetches two steps ahead
-    step<S, true>(acc, f0, f1, L, kt, n_kt, lds0, lds2, lds1, a_off0, b_off0);
-    step<S, true>(acc, f0, f1, L, kt + 1, n_kt, lds1, lds0, lds2, a_off0, b_off0);
-    step<S, true>(acc, f0, f1, L, kt + 2, n_kt, lds2, lds1, lds0, a_off0, b_off0);
+    step<S, true>(acc, f0, f1, L, kt, n_kt, lds0, dst2, lds1, a_off0, b_off0);
+    step<S, true>(acc, f0, f1, L, kt + 1, n_kt, lds1, dst0, lds2, a_off0, b_off0);
+    step<S, true>(acc, f0, f1, L, kt + 2, n_kt, lds2, dst1, lds0, a_off0, b_off0);
   }
   for (; kt < n_kt; kt += 3) {       // the last (up to four) steps
-    step<S, false>(acc, f0, f1, L, kt, n_kt, lds0, lds2, lds1, a_off0, b_off0);
+    step<S, false>(acc, f0, f1, L, kt, n_kt, lds0, dst2, lds1, a_off0, b_off0);
     if (kt + 1 >= n_kt) break;
-    step<S, false>(acc, f0, f1, L, kt + 1, n_kt, lds1, lds0, lds2, a_off0, b_off0);
+    step<S, false>(acc, f0, f1, L, kt + 1, n_kt, lds1, dst0, lds2, a_off0, b_off0);
     if (kt + 2 >= n_kt) break;
-    step<S, false>(acc, f0, f1, L, kt + 2, n_kt, lds2, lds1, lds0, a_off0, b_off0);
+    step<S, false>(acc, f0, f1, L, kt + 2, n_kt, lds2, dst1, lds0, a_off0, b_off0);
   }
 
   // ------------------------------------------------------------------ epilogue

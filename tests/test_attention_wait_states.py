@@ -188,3 +188,16 @@ def test_o_mfmas_have_their_wait_states(attention_asm):
         assert sum(isinstance(x, Ins) and x.mfma and x.in_asm for x in code) >= 32
         assert sum(isinstance(x, Ins) and x.copy and x.in_asm for x in code) >= 16
     assert not found, "\n".join(found[:20])
+
+
+def test_projection_copies_have_their_wait_states(tmp_path):
+    s = str(tmp_path / "project.s")
+    subprocess.run(["hipcc", *build.FLAGS, *build.SOURCE_FLAGS.get("project.hip", []), "-S", "--cuda-device-only",
+                    os.path.join(build.CSRC, "project.hip"), "-o", s], check=True, stdout=subprocess.DEVNULL,
+                   stderr=subprocess.DEVNULL)
+    with open(s) as f:
+        found, kernels = faults(f.read())
+    assert len(kernels) == 4   # 2 tile widths x norm per head or over the row
+    for code in kernels.values():
+        assert sum(isinstance(x, Ins) and x.copy and x.in_asm for x in code) >= 48
+    assert not found, "\n".join(found[:20])
