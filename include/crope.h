@@ -273,12 +273,12 @@ int32_t crope_qkv_project_tile_tokens(int32_t n_tokens, int32_t n_heads, int32_t
  * bf16 of the remainder in the workspace) and a second pass stores the bf16 rounding of their
  * sum times 1/rms: one rounding of the fp32 value up to 2^-17 relative.
  *
- * Which path is faster (one MI355X, bf16): this call ties with a vendor GEMM followed by
- * crope_qk_norm_rotate_append at 12 heads x 4680 tokens with norm_group == 128 (81 against
- * 80 us) and is the slower one there with the row-wide norm (100 us: the second pass and the
- * workspace round trip), at 40 heads x 585 tokens (114 against 88 us) and at 18720 tokens; it
- * is the faster one where the GEMM is small (5 heads x 4680 tokens: 30 against 41 us; 12 heads
- * x 1728 tokens: 34 against 41 us).  Callers who want the fastest path at the large shapes
+ * Which path is faster (one MI355X, bf16, against a vendor GEMM followed by
+ * crope_qk_norm_rotate_append): this call, with norm_group == 128, at widths of 1536 (12 heads x
+ * 1728 tokens 28 against 31 us, x 4680 tokens 78 against 80, x 18720 tokens 258 against 268).  It
+ * is the slower one with the row-wide norm there (37, 94 and 326 against 31, 73 and 270 us: the
+ * second pass and the workspace round trip) and at a width of 5120 (40 heads x 585 tokens 97
+ * against 83 us, 5 heads x 4680 tokens 95 against 89).  Callers who want the fastest path at the large shapes
  * should use the two-kernel sequence.
  *
  *   x              device bf16 [n_tokens][c_in], row stride x_token_stride elements

@@ -97,8 +97,8 @@ struct TileLoader {   // scalars only
 // the compiler turns every counted wait on an LDS read into a wait for all of them.  LDS
 // address of lane i's 16 bytes: M0 + 16*i; M0 is an input operand bound to that register, the
 // s_nop covers the wait state after its write.  Base and step are scalar (a buffer and its scalar offset), so that a
-// copy costs no vector instruction and two scalar ones (585 rows x 40 heads 106.9 -> 101.7 us, 600 x 8 17.7 -> 16.3;
-// with 64-bit bases and LDS addresses taken from pointers it were eight).  A vector instruction that wrote one of the
+// copy costs no vector instruction and two scalar ones (585 rows x 40 heads 106.9 -> 101.7 us, 600 x 8 17.7 -> 16.3,
+// W in the last-level cache; with 64-bit bases and LDS addresses taken from pointers it were eight).  A vector instruction that wrote one of the
 // buffer's words would need five wait states that the compiler does not insert here: the words are formed ahead
 // of the loop, and the tests check the assembly.
 __device__ __forceinline__ void copy16(u32x4_t buf, uint32_t lane_off, uint32_t k_off /* wave-uniform */,
