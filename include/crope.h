@@ -275,7 +275,8 @@ int32_t crope_qkv_project_tile_tokens(int32_t n_tokens, int32_t n_heads, int32_t
  *
  * Which path is faster (one MI355X, bf16, against a vendor GEMM followed by
  * crope_qk_norm_rotate_append): this call, with norm_group == 128, at widths of 1536 (12 heads x
- * 1728 tokens 28 against 31 us, x 4680 tokens 78 against 80, x 18720 tokens 258 against 268).  It
+ * 1728 tokens 28 against 31 us, x 18720 tokens 258 against 268; x 4680 tokens they tie, 76 to 80
+ * against 77 to 80 on different boards).  It
  * is the slower one with the row-wide norm there (37, 94 and 326 against 31, 73 and 270 us: the
  * second pass and the workspace round trip) and at a width of 5120 (40 heads x 585 tokens 97
  * against 83 us, 5 heads x 4680 tokens 95 against 89).  Callers who want the fastest path at the large shapes
