@@ -141,7 +141,9 @@ float crope_folded_q_scale(float softmax_scale);
  * q_scale = crope_folded_q_scale(softmax scale). */
 #define CROPE_SCALE_FOLDED 0.0f
 
-/* Bytes of scratch chunk_attention needs for this problem size (may be 0). */
+/* Bytes of scratch that chunk_attention's fastest work division of this problem size needs (may be 0): up
+ * to 16 ranges of 520 bytes per query and head.  The number belongs to this build of the library: it changes
+ * when the division is fitted to other kernels. */
 size_t chunk_attention_workspace_bytes(int32_t n_q, int32_t n_heads, int64_t n_keys);
 
 /* Attention of the chunk's rotated queries over every visible cache row (Algorithm 3
@@ -162,6 +164,9 @@ size_t chunk_attention_workspace_bytes(int32_t n_q, int32_t n_heads, int64_t n_k
  *   lse_or_null    device fp32 [n_heads][n_q], natural-log sum-exp of the scaled scores
  *   workspace      device scratch of >= chunk_attention_workspace_bytes(...) bytes, 16-byte
  *                  aligned; may be NULL when that size is 0.  Contents are undefined after.
+ *                  Where the division before this one wanted less (1664x960, 21 frames: none
+ *                  for 234 MB now), that is still enough: the call runs the fastest division
+ *                  that fits.
  * n_q == 0 is a no-op.  Limits (CROPE_ERANGE beyond): cache capacity < 2^31 rows, cache token
  * stride <= 2^24 elements, at most 2^30 visible keys.  Head strides below 128 are CROPE_EINVAL. */
 int chunk_attention(

@@ -249,10 +249,14 @@ int attention_impl(const void* q, crope_strides q_strides, int32_t n_q, int32_t 
     a.segs.end[i] = (int32_t)n_keys;
   }
   for (int i = n_segs; i < crope::kMaxSegments; ++i) a.segs.base[i] = a.segs.base[n_segs - 1];
-  const size_t need = limited ? 0 : crope::attention_workspace_bytes(n_q > 0 ? n_q : 1, n_heads, n_keys, want);
-  if (need > 0 && (!workspace || workspace_bytes < need))
-    return fail(CROPE_EWORKSPACE, "workspace has %zu bytes, needs %zu", workspace ? workspace_bytes : 0,
-                need);
+  const int32_t size_q = n_q > 0 ? n_q : 1;
+  const size_t have = workspace ? workspace_bytes : 0;
+  const size_t need = limited ? 0 : crope::attention_workspace_bytes(size_q, n_heads, n_keys, want);
+  if (have < need) {
+    if (have < crope::attention_least_workspace_bytes(size_q, n_heads, n_keys, want))
+      return fail(CROPE_EWORKSPACE, "workspace has %zu bytes, needs %zu", have, need);
+    want = crope::attention_plan(size_q, n_heads, n_keys, want, have);   // the fastest division that fits
+  }
   if (n_q == 0) { g_err[0] = 0; return CROPE_OK; }
   a.q = (const uint16_t*)q; a.q_tok = q_strides.token; a.q_head = q_strides.head;
   a.n_q = n_q; a.n_heads = n_heads;

@@ -2,6 +2,7 @@
 // Not installed; include/crope.h is the public boundary.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 #include "../../include/crope.h"
 #include "fastdiv.h"
@@ -84,13 +85,15 @@ hipError_t launch_rope(const RopeArgs& a, hipStream_t st);
 int rope_max_heads();
 // 32-query units per work-group (4 or 8) and key splits (1..16); 0 = let the library choose
 struct AttnPlan { int waves; int splits; };
-AttnPlan attention_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
+AttnPlan attention_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan want, size_t max_bytes = SIZE_MAX);
 // chunk_attention_static: bytes by which a size is taken (at most its buffer) or refused, and the plan of one
 // that is taken: attention_plan's, or the best one whose partial results fit the buffer
 size_t attention_static_need(int n_q, int n_heads, int64_t n_keys);
 AttnPlan attention_static_plan(int n_q, int n_heads, int64_t n_keys);
 hipError_t launch_attention(const AttnArgs& a, AttnPlan want, hipStream_t st);
 size_t attention_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
+// the smallest workspace that is taken: that of the division now or of the one before it, whichever is less
+size_t attention_least_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
 int project_tile_tokens(int n_tokens, int n_heads, int c_in);   // width of launch_project's tiles
 hipError_t launch_project(const ProjArgs& a, hipStream_t st);
 size_t project_workspace_bytes(int n_tokens, int n_heads, bool per_head_norm);

@@ -1,7 +1,10 @@
-// Which sizes chunk_attention_static takes.  Two estimates that once divided the calls and no longer do: a
-// size is taken if the partial results of the division that either of them picks fit the built-in buffer.  They
-// stay as they were, so that the sizes a program may rely on don't change whenever the division that is
-// really made (choose_plan in attention.hip) is fitted to another kernel.
+// Which scratch a call is taken with.  Two estimates that once divided the calls and no longer do.  They stay as
+// they were, so that what a program may rely on doesn't change whenever the division that is really made
+// (choose_plan in attention.hip) is fitted to another kernel:
+//   * chunk_attention_static takes a size if the partial results of the division that either of them picks fit
+//     the built-in buffer;
+//   * chunk_attention takes a workspace of the size that the second one asks for, though the fastest division
+//     now wants more (1664x960, last chunk: none then, 234 MB for two splits now).
 #pragma once
 #include <algorithm>
 #include <stddef.h>
@@ -39,8 +42,9 @@ bool always_fitted_static(int n_q, int n_heads, int64_t n_keys) {
   return partial_bytes(best, n_q, n_heads) <= (size_t)CROPE_STATIC_SCRATCH_BYTES;
 }
 
-// The second one: microseconds, with rates of the kernel of its day.  Returns its number of splits.
-int second_static_splits(int n_q, int n_heads, int64_t n_keys) {
+// The second one: microseconds, with rates of the kernel of its day.  Returns its number of splits; `waves` pins
+// the work-group's size where it isn't 0.
+int second_splits(int n_q, int n_heads, int64_t n_keys, int waves) {
   const int n_tiles = (int)((n_keys + kUnitKeys - 1) / kUnitKeys);
   int best = 1;
   const bool huge = (int64_t)n_heads * n_keys > 3000000;
@@ -48,6 +52,7 @@ int second_static_splits(int n_q, int n_heads, int64_t n_keys) {
   const bool from_hbm = n_q <= 256 && (int64_t)n_heads * n_keys * 4 * kHeadDim > (32 << 20) && (!huge || fitted);
   double best_cost = 1e30;
   for (int nw = 4; nw <= 8; nw += 4) {
+    if (waves && nw != waves) continue;
     const int bm = 32 * nw;
     const int64_t units = (int64_t)((n_q + bm - 1) / bm) * n_heads;
     for (int s = 1; s <= kMaxSplits && s <= n_tiles; ++s) {
