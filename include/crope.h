@@ -222,9 +222,9 @@ int chunk_attention_planned(
  * division and bit-identical results wherever chunk_attention's scratch fits the buffer.
  *   - CROPE_EWORKSPACE, before anything is launched, if the problem would need more scratch
  *     than the buffer holds (chunk_attention_workspace_bytes(...) > CROPE_STATIC_SCRATCH_BYTES;
- *     300 queries x 64 heads x 60000 keys), except for sizes that fitted it under the library's first
- *     work division: those run with the best division that fits (a 1280x720 chunk: 10800 queries x
- *     12 heads, unsplit).  The 40-head 585-query x 32760-key rank share needs 23 MiB.
+ *     300 queries x 64 heads x 60000 keys), except for sizes that fitted it under one of the library's
+ *     earlier work divisions: those run with the best division that fits (a 1280x720 chunk: 10800
+ *     queries x 12 heads, unsplit).  The 40-head 585-query x 32760-key rank share needs 23 MiB.
  *   - The first call on a GPU looks the buffer's device address up (a runtime query, no
  *     allocation) and keeps it for later calls; call with that GPU current.  Make that first
  *     call outside any graph capture.

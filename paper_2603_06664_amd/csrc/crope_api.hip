@@ -363,11 +363,11 @@ int chunk_attention_static(const void* q, crope_strides q_strides, int32_t n_q, 
     int64_t n_keys = 0;
     for (int i = 0; i < n_segs; ++i) n_keys += segs[i].len > 0 ? segs[i].len : 0;
     if (n_keys > 0 && n_keys <= ((int64_t)1 << 30)) {
-      const size_t need = crope::attention_static_need(n_q, n_heads, n_keys);
-      if (need > kStaticScratchBytes)
+      if (!crope::attention_static_takes(n_q, n_heads, n_keys))
         return fail(CROPE_EWORKSPACE,
                     "chunk_attention_static: this problem needs %zu bytes of scratch, the built-in "
-                    "buffer holds %zu; use chunk_attention with a caller-provided workspace", need, kStaticScratchBytes);
+                    "buffer holds %zu; use chunk_attention with a caller-provided workspace",
+                    crope::attention_workspace_bytes(n_q, n_heads, n_keys, crope::AttnPlan{0, 0}), kStaticScratchBytes);
       const crope::AttnPlan p = crope::attention_static_plan(n_q, n_heads, n_keys);
       plan = crope_attention_plan{p.waves, p.splits};
     }

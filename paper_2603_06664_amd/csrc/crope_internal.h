@@ -86,9 +86,9 @@ int rope_max_heads();
 // 32-query units per work-group (4 or 8) and key splits (1..16); 0 = let the library choose
 struct AttnPlan { int waves; int splits; };
 AttnPlan attention_plan(int n_q, int n_heads, int64_t n_keys, AttnPlan want, size_t max_bytes = SIZE_MAX);
-// chunk_attention_static: bytes by which a size is taken (at most its buffer) or refused, and the plan of one
-// that is taken: attention_plan's, or the best one whose partial results fit the buffer
-size_t attention_static_need(int n_q, int n_heads, int64_t n_keys);
+// chunk_attention_static: whether a size is taken, and the plan of one that is: attention_plan's, or the best one
+// whose partial results fit the buffer
+bool attention_static_takes(int n_q, int n_heads, int64_t n_keys);
 AttnPlan attention_static_plan(int n_q, int n_heads, int64_t n_keys);
 hipError_t launch_attention(const AttnArgs& a, AttnPlan want, hipStream_t st);
 size_t attention_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);

@@ -1,8 +1,8 @@
 // Which scratch a call is taken with.  Two estimates that once divided the calls and no longer do.  They stay as
 // they were, so that what a program may rely on doesn't change whenever the division that is really made
 // (choose_plan in attention.hip) is fitted to another kernel:
-//   * chunk_attention_static takes a size if the partial results of the division that either of them picks fit
-//     the built-in buffer;
+//   * chunk_attention_static takes a size if the partial results of the division that either of them or
+//     choose_plan picks fit the built-in buffer;
 //   * chunk_attention takes a workspace of the size that the second one asks for, though the fastest division
 //     now wants more (1664x960, last chunk: none then, 234 MB for two splits now).
 #pragma once

@@ -40,6 +40,30 @@ def test_sizes_that_are_refused(size):
     assert _static_call(*size) == EWORKSPACE
 
 
+# unsplit now, but too large for the buffer in the divisions before
+@pytest.mark.parametrize("size", [(2887, 25, 4442), (9402, 9, 6252), (5237, 15, 5422)])
+def test_sizes_whose_present_division_fits(size):
+    import paper_2603_06664_amd as P
+    assert P.chunk_attention_workspace_bytes(*size) == 0
+    assert _static_call(*size) != EWORKSPACE
+
+
+def test_a_size_whose_workspace_fits_is_never_refused():
+    """The rule of the header: a refused size needs more scratch than the buffer holds, and the message says how much."""
+    import paper_2603_06664_amd as P
+    rng = np.random.default_rng(506)
+    refused = 0
+    for _ in range(20000):
+        size = [int(round(np.exp(rng.uniform(np.log(lo), np.log(hi))))) for lo, hi in ((200, 20000), (2, 64), (500, 175000))]
+        if _static_call(*size) != EWORKSPACE:
+            continue
+        refused += 1
+        need = P.chunk_attention_workspace_bytes(*size)
+        assert need > P.chunk_attention_static_capacity(), size
+        assert "needs %d bytes" % need in B.crope_last_error(), size
+    assert refused > 100
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("folded", [False, True])
 def test_call_divided_less_matches_the_oracle(folded):
