@@ -164,9 +164,9 @@ size_t chunk_attention_workspace_bytes(int32_t n_q, int32_t n_heads, int64_t n_k
  *   lse_or_null    device fp32 [n_heads][n_q], natural-log sum-exp of the scaled scores
  *   workspace      device scratch of >= chunk_attention_workspace_bytes(...) bytes, 16-byte
  *                  aligned; may be NULL when that size is 0.  Contents are undefined after.
- *                  Where the division before this one wanted less (1664x960, 21 frames: none
- *                  for 234 MB now), that is still enough: the call runs the fastest division
- *                  that fits.
+ *                  Where one of the two divisions before this one wanted less (1664x960, 21
+ *                  frames: none for 234 MB now), that is still enough: the call runs the
+ *                  fastest division that fits.
  * n_q == 0 is a no-op.  Limits (CROPE_ERANGE beyond): cache capacity < 2^31 rows, cache token
  * stride <= 2^24 elements, at most 2^30 visible keys.  Head strides below 128 are CROPE_EINVAL. */
 int chunk_attention(

@@ -92,7 +92,7 @@ bool attention_static_takes(int n_q, int n_heads, int64_t n_keys);
 AttnPlan attention_static_plan(int n_q, int n_heads, int64_t n_keys);
 hipError_t launch_attention(const AttnArgs& a, AttnPlan want, hipStream_t st);
 size_t attention_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
-// the smallest workspace that is taken: that of the division now or of the one before it, whichever is less
+// the smallest workspace that is taken: the least that the division now or one of the two before it wants
 size_t attention_least_workspace_bytes(int n_q, int n_heads, int64_t n_keys, AttnPlan want);
 int project_tile_tokens(int n_tokens, int n_heads, int c_in);   // width of launch_project's tiles
 hipError_t launch_project(const ProjArgs& a, hipStream_t st);

@@ -12,3 +12,11 @@ def test_one_query_tile_fills_the_gpu_by_splits(n_q, n_heads, n_keys):
     16 splits that there are (measured: 4 to 6 splits of 40 heads and 16 of 12 are the fastest)."""
     plan = P.chunk_attention_choose_plan(n_q, n_heads, n_keys)
     assert plan[1] == 16 or 192 <= n_heads * plan[1] <= 256, plan
+
+
+@pytest.mark.parametrize("n_q,n_heads,n_keys", [(262, 22, 27422), (257, 38, 17991), (269, 15, 67003), (545, 44, 15519),
+                                                (293, 26, 102830), (351, 37, 44483), (268, 49, 36223), (384, 49, 27425)])
+def test_few_query_tiles_over_caches_beyond_the_last_level(n_q, n_heads, n_keys):
+    """K and V above 256 MB: 128-query work-groups read them twice as often and lose 6 to 20 % (measured)."""
+    assert n_heads * n_keys * 512 > 256 << 20
+    assert P.chunk_attention_choose_plan(n_q, n_heads, n_keys)[0] == 8

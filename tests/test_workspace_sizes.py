@@ -1,4 +1,4 @@
-"""A workspace of the size that chunk_attention once asked for is still taken where the present division wants
+"""A workspace of a size that chunk_attention once asked for is still taken where the present division wants
 more: the call runs the fastest division that fits."""
 import ctypes
 
@@ -11,7 +11,7 @@ EWORKSPACE = -5
 ROW = 130 * 4   # bytes of a query's partial result
 
 # n_q, heads, keys, splits at that time (1 = no workspace)
-ONCE = [(897, 7, 1794, 2), (4680, 5, 32760, 2), (18720, 12, 131040, 1), (10800, 12, 75600, 2), (9048, 29, 108576, 1),
+ONCE = [(545, 44, 15519, 1), (351, 37, 44483, 2), (897, 7, 1794, 2), (4680, 5, 32760, 2), (18720, 12, 131040, 1), (10800, 12, 75600, 2), (9048, 29, 108576, 1),
         (17160, 38, 102960, 1)]
 
 
