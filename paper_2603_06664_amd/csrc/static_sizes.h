@@ -110,5 +110,12 @@ int third_splits(int n_q, int n_heads, int64_t n_keys, int waves) {
   return best;
 }
 
+bool always_refused_static(int n_q, int n_heads, int64_t n_keys) {
+  const size_t buffer = (size_t)CROPE_STATIC_SCRATCH_BYTES;
+  return !always_fitted_static(n_q, n_heads, n_keys) &&
+         partial_bytes(second_splits(n_q, n_heads, n_keys, 0), n_q, n_heads) > buffer &&
+         partial_bytes(third_splits(n_q, n_heads, n_keys, 0), n_q, n_heads) > buffer;
+}
+
 }  // namespace
 }  // namespace crope

@@ -20,3 +20,12 @@ def test_few_query_tiles_over_caches_beyond_the_last_level(n_q, n_heads, n_keys)
     """K and V above 256 MB: 128-query work-groups read them twice as often and lose 6 to 20 % (measured)."""
     assert n_heads * n_keys * 512 > 256 << 20
     assert P.chunk_attention_choose_plan(n_q, n_heads, n_keys)[0] == 8
+
+
+@pytest.mark.parametrize("n_q,n_heads,n_keys", [(9048, 29, 108576), (17160, 38, 102960), (4000, 40, 120000)])
+def test_large_caches_take_any_number_of_splits(n_q, n_heads, n_keys):
+    """More than 3 M heads x keys, taken by chunk_attention_static: no jump to 8 splits where fewer are as fast (9048
+    queries: 10.93 ms in 8 splits and 1.1 GB of scratch, 10.90 in 6)."""
+    assert n_heads * n_keys > 3000000
+    splits = P.chunk_attention_choose_plan(n_q, n_heads, n_keys)[1]
+    assert 1 <= splits < 8, splits
