@@ -29,3 +29,10 @@ def test_large_caches_take_any_number_of_splits(n_q, n_heads, n_keys):
     assert n_heads * n_keys > 3000000
     splits = P.chunk_attention_choose_plan(n_q, n_heads, n_keys)[1]
     assert 1 <= splits < 8, splits
+
+
+@pytest.mark.parametrize("n_q,n_heads,n_keys", [(50432, 4, 8192), (83200, 4, 30000)])
+def test_nearly_empty_last_round_among_several(n_q, n_heads, n_keys):
+    """3.08 and 5.08 rounds: splitting to fill the last of them loses (measured unsplit and in 2 splits: 674 and 723 us,
+    3802 and 3953)."""
+    assert P.chunk_attention_choose_plan(n_q, n_heads, n_keys)[1] == 1
