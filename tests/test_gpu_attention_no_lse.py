@@ -1,5 +1,6 @@
 """Unsplit calls of the 256-query shape that ask for no log-sum-exp: they do without the sum of the unrounded
-probabilities, which also took part in the denominator's fallback and in the range check."""
+probabilities, which also took part in the denominator's fallback and in the range check.  (The limited calls here are
+too small for that shape and run in 128-query work-groups.)"""
 import numpy as np
 import pytest
 
