@@ -193,8 +193,8 @@ struct Narrow {
   }
   __device__ __forceinline__ float range_sum(int) const { return across_sum(l_run[0]); }
 
-  // k_blk, v_blk: byte offsets of K_b and V_{b-1} from k_off / v_off, which move on by k_flip (exclusive or) and
-  // v_shift behind their last use; key0: index of K_b's first key; lim: the lane's queries see keys [0, lim).
+  // k_blk, v_blk: byte offsets of K_b and V_{b-1} from k_off / v_off, which move on by k_flip (exclusive or: the K
+  // tiles start at a multiple of twice their size) and v_shift behind their last use; key0: index of K_b's first key; lim: the lane's queries see keys [0, lim).
   // FOLDED: the queries already carry scale*log2(e), so the MFMA result is the exponent itself once the
   // accumulators start from minus the reference; otherwise scores are raw and each costs one fma.
   template <int PAR, bool DO_PV, bool DO_S, bool DO_SM, bool READ_V, bool MASK, bool FOLDED, bool SUM, class FEED>
