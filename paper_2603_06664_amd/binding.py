@@ -6,13 +6,15 @@ arithmetic happens in the HIP kernels.  There is no CPU fallback: if the library
 loaded, the call raises.
 
 The per-chunk calls hand plain arguments (torch tensors, ints, floats, lists of pairs) to the library through
-the _fastcall extension; anything else goes through ctypes, with the same results and errors.  One append and one
+the _fastcall extension; anything else goes through ctypes, with the same results and errors, and so does everything where
+that extension is missing or of another torch (a warning says so).  One append and one
 attention call of 24 tokens: 26 us of host time through ctypes, 10.6 us through the extension.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional, Sequence, Tuple
 
@@ -78,9 +80,11 @@ def _load():
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  (loads the HIP runtime the library binds to)
-    if not os.path.exists(_LIB_PATH) or not os.path.exists(_FAST_PATH):
-        from . import build as _build
+    from . import build as _build
+    if not os.path.exists(_LIB_PATH):
         _build.build()
+    elif not os.path.exists(_FAST_PATH):
+        _build.build_fastcall()
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     lib.crope_last_error.restype = ctypes.c_char_p
@@ -131,9 +135,23 @@ def _load():
     lib.crope_qkv_project_norm_rotate_append.argtypes = [
         ctypes.POINTER(_Desc), vp, vp, i64, vp, vp, i32, vp, vp, f32, i32, i32, i32, i32, i32, i32,
         i32, vp, _Strides, vp, vp, _Strides, i64, i64, vp, ctypes.c_size_t, vp]
-    _fast = _load_fastcall(lib)
+    try:
+        if not _build.fastcall_current():
+            raise ImportError("not built for %s" % _build.fastcall_tag())
+        _fast = _load_fastcall(lib)
+    except Exception as e:   # the library is complete without it
+        warnings.warn("%s does not load (%s): calls go through ctypes, at some 8 us more of host time each"
+                      % (_FAST_PATH, e))
+        _fast = _CtypesOnly()
     _lib = lib
     return lib
+
+
+class _CtypesOnly:
+    """Stands in for the extension where there is none."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
 
 
 def _load_fastcall(lib):

@@ -5,6 +5,8 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -32,7 +34,7 @@ SOURCE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 def _stale() -> bool:
     built = (LIB, CEILINGS_LIB, FASTCALL)
-    if not all(os.path.exists(f) for f in built):
+    if not all(os.path.exists(f) for f in built) or not fastcall_current():
         return True
     t = min(os.path.getmtime(f) for f in built)
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h", ".cpp"))] + \
@@ -40,15 +42,46 @@ def _stale() -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def fastcall_tag() -> str:
+    """What the extension is compiled for: torch's C++ classes are not the same from version to version."""
+    import torch
+    return "torch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
+
+
+def fastcall_current() -> bool:
+    if not os.path.exists(FASTCALL):
+        return False
+    with open(FASTCALL, "rb") as f:
+        return fastcall_tag().encode() in f.read()
+
+
 def _fastcall_command() -> list:
     import sysconfig
     import torch
     from torch.utils import cpp_extension
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DCROPE_FASTCALL_FOR="%s"' % fastcall_tag(),
             *[f for d in cpp_extension.include_paths() for f in ("-isystem", d)],
             "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, FASTCALL_SOURCE), "-o", FASTCALL + ".tmp",
             *["-L" + d for d in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
+def build_fastcall() -> bool:
+    """Compile the extension.  It needs g++ and the headers of torch and Python, which the library does not: where that
+    fails the binding does without, so it is a warning, and no extension of older sources stays behind."""
+    try:
+        cmd = _fastcall_command()
+        p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        why = None if p.returncode == 0 else "%s failed: %s\n%s" % (cmd[0], " ".join(cmd), p.stdout)
+    except Exception as e:   # no compiler, or a torch without its headers
+        why = "%s: %s" % (type(e).__name__, e)
+    if why is None:
+        os.replace(FASTCALL + ".tmp", FASTCALL)
+        return True
+    if os.path.exists(FASTCALL):
+        os.remove(FASTCALL)
+    warnings.warn("%s was not built: %s" % (os.path.basename(FASTCALL), why))
+    return False
 
 
 def build(force: bool = False, verbose: bool = False) -> str:
@@ -61,13 +94,12 @@ def build(force: bool = False, verbose: bool = False) -> str:
     cmd = ["hipcc", *[f for f in FLAGS if f not in ("-fPIC", "-fvisibility=hidden")],
            os.path.join(CSRC, ISSUE_BENCH_SOURCE), "-o", ISSUE_BENCH]
     procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    cmd = _fastcall_command()
-    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
         cmd = ["hipcc", *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    build_fastcall()   # while hipcc runs
     for cmd, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
@@ -81,7 +113,6 @@ def build(force: bool = False, verbose: bool = False) -> str:
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
     os.replace(CEILINGS_LIB + ".tmp", CEILINGS_LIB)
-    os.replace(FASTCALL + ".tmp", FASTCALL)
     return LIB
 
 

@@ -11,6 +11,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include "../../include/crope.h"
 
+// The torch and Python that this is compiled for (build.py): looked for in the file before it is loaded.
+extern "C" __attribute__((visibility("default"), used)) const char crope_fastcall_for[] = CROPE_FASTCALL_FOR;
+
 namespace {
 
 decltype(&crope_qk_norm_rotate_append) p_append;
