@@ -187,7 +187,8 @@ typedef struct {
 
 /* Resolve a plan: on entry the non-zero fields of *plan are kept, on return every field holds
  * the value chunk_attention_planned would use for this problem size (all zeros on entry gives
- * the plan chunk_attention itself uses).  CROPE_EINVAL for a null pointer, non-positive sizes
+ * the plan chunk_attention itself uses with
+ * a workspace of chunk_attention_workspace_bytes(...)).  CROPE_EINVAL for a null pointer, non-positive sizes
  * or field values outside the ranges above. */
 int chunk_attention_choose_plan(int32_t n_q, int32_t n_heads, int64_t n_keys,
                                 crope_attention_plan* plan);
