@@ -470,6 +470,7 @@ int crope_qkv_project_norm_rotate_append(
   a.per_head_norm = per_head ? 1 : 0;
   a.n_tokens = n_tokens; a.n_heads = n_heads; a.grid_h = grid_h; a.grid_w = grid_w;
   a.start_frame = start_frame; a.token_offset = token_offset;
+  a.div_hw = crope::make_fastdiv((uint32_t)hw); a.div_w = crope::make_fastdiv((uint32_t)grid_w);
   a.q_out = (uint16_t*)q_out; a.qo_tok = q_out_strides.token; a.qo_head = q_out_strides.head;
   a.k_cache = (uint16_t*)k_cache; a.v_cache = (uint16_t*)v_cache;
   a.c_tok = cache_strides.token; a.c_head = cache_strides.head;

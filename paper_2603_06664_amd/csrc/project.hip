@@ -7,19 +7,20 @@
 // fragments as they lie in memory.  The product is formed transposed, C^T = W . x^T
 // (channels = MFMA rows, tokens = columns): an accumulator lane then holds 4 consecutive
 // channels of ONE token, i.e. two whole rotation pairs, and the epilogue needs no cross-lane
-// traffic for the rotation; the bf16 tile is then transposed through LDS and leaves in whole
-// 256-byte (token, head) rows.
+// traffic for the rotation.
 //
-// A work-group owns 128 output channels (one head of q, k or v) x 256 tokens (8 waves of 64 x 64, two
-// per SIMD) or x 192 tokens (4 waves of 64 x 96, one per SIMD); launch_project says which one when.
-// What bounds a full chip is the 256-wide loop at 1.2 PFLOP/s (18720 x 1536 -> 4608, row-wide norm
-// and all epilogues included 336 us = 0.79 PFLOP/s; 344 us before the copies and fragment reads were
-// spread between the MFMAs one by one), and then the serial epilogue; what bounds a small call is how
-// its tiles divide over 256 CUs.  The reduction runs in steps of
-// 64 through three LDS stages filled by global_load_lds (16 B per lane, no registers), one
-// barrier per step.  LDS rows are 128 B; 16-byte chunk c of row r sits at slot
-// c ^ ((r >> 1) & 7), which makes the fragment reads (32 rows x 16 B per half wave)
-// conflict-free.
+// A work-group is 8 waves of 64 channels x up to 128 tokens (v_mfma_f32_16x16x32_bf16, two waves per SIMD) and owns two
+// heads of q, k or v x 256 or 192 tokens, or one head; launch_project says which width when, make_tiles
+// how many of which.  What bounds the loop is the way from the L2 to LDS: with all CUs copying it carries 24 TB/s (39 bytes per
+// clock and CU) in requests of 128 bytes and 13.5 TB/s in requests of 64, whatever the stride of the rows.  Hence two heads per
+// work-group (32 to 37 bytes per clock at full MFMA rate; one head 48 to 53), and reduction steps of 64, whose LDS
+// rows are one 128-byte request each (a version with steps of 32 and two work-groups per CU: 105 us where this takes 92).
+// Then latency: W and x have rings of their own in LDS, as deep as 160 KB allow (see Shape, half_step).
+// 4680 tokens x 12 heads, c_in 1536 92 -> 84 us (norm per head 72 -> 64), 585 x 40 heads, 5120 128 -> 109 (113 -> 94), 1320 x 16
+// heads, 2048 57 -> 49 (46 -> 37), 24 x 2 heads, 256 14.3 -> 8.3, against one head per work-group in 32x32x16 MFMAs with a three-stage
+// ring for both operands and the epilogue's tables and tile through LDS.
+// LDS rows are 128 B; 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7), which makes the fragment reads (16 rows x
+// 16 B per quarter wave) conflict-free.
 //
 // RMSNorm over one head is local to the tile and fully fused.  RMSNorm over the token's
 // whole H*128 vector needs every head's sum of squares: the rotation commutes with the
@@ -36,11 +37,10 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-
-#define LDS_ADDR(p) ((uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)(p)))
+typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   f32x2_t f = {lo, hi};
@@ -49,56 +49,68 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-__device__ __forceinline__ float sum_across_halves(float x) {
-  const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+// sum over the lanes l, l^16, l^32, l^48
+__device__ __forceinline__ float sum_across_rows(float x) {
+  u32x2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-constexpr int kTileCh = 128;    // output channels per work-group: one head
+constexpr int kTileCh = 128;    // one head
 constexpr int kStepK = 64;      // reduction elements per LDS stage
 constexpr int kRowB = kStepK * 2;             // 128 B per LDS row
-constexpr int kStageA = kTileCh * kRowB;      // 16 KB
-constexpr int kOutRowB = kTileCh * 2 + 16;    // bf16 output tile row in LDS, padded against bank conflicts
-constexpr int kAngRowB = 64 * 8 + 16;         // one token's 64 (cos, sin) pairs in LDS, padded (16-byte rows)
-constexpr int kXcds = 8;
-constexpr int kTokGroup = 4;    // token tiles walked together with 8 channel tiles by one XCD's CUs
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kXcds = 8, kCusPerXcd = 32;
+constexpr int kTokGroup = 4;    // token tiles walked together with 8 pairs of heads by one XCD's CUs
 
+// Units of work, per XCD a run of (pair of heads, token tile): the first `doubles` are one work-group's each, the others two's.
 struct ProjTiles {
-  int ch_tiles, tok_tiles, total, per_xcd;
-  int wgs_per_xcd;   // work-groups launched per XCD (at most its 32 CUs)
+  int ch_tiles, ch_pairs, tok_tiles, total, per_xcd, doubles;
 };
 
-// Shape of a work-group: 2 (channel halves) x WT waves, each 64 channels x 32*TT tokens.
-template <int WT_, int TT_>
+// A tile of 64*WC channels (one head or two) x 16*TT*(8/WC) tokens: 8 waves of 64 channels x 16*TT tokens.
+template <int WC_, int TT_>
 struct Shape {
-  static constexpr int WT = WT_, TT = TT_;
-  static constexpr int kWaves = 2 * WT, kThreads = 64 * kWaves;
-  static constexpr int kWaveTok = 32 * TT, kTileTok = kWaveTok * WT;
-  static constexpr int kACopies = kTileCh / (8 * kWaves);   // copies per wave and stage of the W tile
-  static constexpr int kCopies = kACopies + 2 * TT;         // and of the x tile behind it
-  static constexpr int kStage = kStageA + kTileTok * kRowB;
+  static constexpr int WC = WC_, TT = TT_, WT = kWaves / WC;
+  static constexpr int kCh = 64 * WC, kWaveTok = 16 * TT, kTileTok = WT * kWaveTok;
+  static constexpr int kStageA = kCh * kRowB, kStageB = kTileTok * kRowB;
+  // places for W and, behind them, for x: as many as 160 KB hold; one head's tiles run alone on a CU or nearly so, where
+  // latency is all that counts
+  static constexpr int kAStages = WC == 4 ? 3 : 4, kBStages = WC == 4 ? 2 : kTileTok > 192 ? 3 : 4;
+  static constexpr int kLds = kAStages * kStageA + kBStages * kStageB;
+  static constexpr int kACopies = kCh / 64, kBCopies = kTileTok / 64;   // per wave and stage
+  static constexpr int kMfmas = 4 * TT, kReads = 4 + TT;       // per wave and half step
+  static_assert(kTileTok % 64 == 0, "copies are whole kilobytes of every wave");
+  // W of step kt+kAStages-1 is requested in the first half of step kt, x of step kt+kBStages in the second.  Copies that may
+  // be in flight in the middle of step kt, when those of step kt+1 have to have landed: what was requested, in halves of
+  // steps, after the later one of W and x of step kt+1
+  static constexpr int in_flight() {
+    const int a1 = 2 * (2 - kAStages), b1 = 2 * (1 - kBStages) + 1, t = a1 > b1 ? a1 : b1;
+    int n = 0;
+    for (int h = t + 1; h <= 0; ++h) n += h % 2 == 0 ? kACopies : kBCopies;
+    return n;
+  }
 };
 
 template <class S>
 struct TileLoader {   // scalars only
   u32x4_t a_buf;           // W from the tile's first channel row on
   u32x4_t b_buf;           // x from the tile's first token row on
-  // per-lane byte offsets of the lane's chunk for load instruction t: row 8*wave + lane/8 + 8*waves*t
+  // per-lane byte offsets of the lane's chunk for load instruction t: row 8*wave + lane/8 + 64*t
   uint32_t a_off[S::kACopies];
-  uint32_t b_off[2 * S::TT];
-  int lds_off;             // wave * 1024
+  uint32_t b_off[S::kBCopies];
 };
 
-// Copy instruction t of wave w covers tile rows 8*(w + waves*t) .. +7 (1 KB of LDS): lane i carries
-// the chunk that belongs at (row 8*(w + waves*t) + i/8, slot i%8).  ((row >> 1) & 7) = (i>>4) | 4*(w&1)
+// Copy instruction t of wave w covers tile rows 8*(w + 8*t) .. +7 (1 KB of LDS): lane i carries
+// the chunk that belongs at (row 8*(w + 8*t) + i/8, slot i%8).  ((row >> 1) & 7) = (i>>4) | 4*(w&1)
 // does not depend on t.  Token rows past the end re-read the last token (clamped when the
 // offsets are formed); their results are never stored.
 // The copy is inline assembly, not the compiler's builtin: while a builtin copy is in flight
 // the compiler turns every counted wait on an LDS read into a wait for all of them.  LDS
 // address of lane i's 16 bytes: M0 + 16*i; M0 is an input operand bound to that register, the
 // s_nop covers the wait state after its write.  Base and step are scalar (a buffer and its scalar offset), so that a
-// copy costs no vector instruction and two scalar ones (585 rows x 40 heads 106.9 -> 101.7 us, 600 x 8 17.7 -> 16.3,
-// W in the last-level cache; with 64-bit bases and LDS addresses taken from pointers it were eight).  A vector instruction that wrote one of the
+// copy costs no vector instruction and two scalar ones.  A vector instruction that wrote one of the
 // buffer's words would need five wait states that the compiler does not insert here: the words are formed ahead
 // of the loop, and the tests check the assembly.
 __device__ __forceinline__ void copy16(u32x4_t buf, uint32_t lane_off, uint32_t k_off /* wave-uniform */,
@@ -114,32 +126,30 @@ __device__ __forceinline__ u32x4_t raw_buffer(const uint8_t* base /* wave-unifor
                  (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)), 0xffffffffu, 0x00020000u};
 }
 
-// copy i of reduction step kt: the W tile first, then the x tile behind it in the stage
+// copy i of the W tile, of the x tile, of reduction step kt; dst: the place + 1024 * wave
 template <class S>
-__device__ __forceinline__ void load_copy(const TileLoader<S>& L, int kt, uint32_t stage, int i) {
-  const uint32_t k_off = (uint32_t)kt * kRowB;
-  if (i < S::kACopies) copy16(L.a_buf, L.a_off[i], k_off, stage + L.lds_off + i * (S::kWaves * 1024));
-  else copy16(L.b_buf, L.b_off[i - S::kACopies], k_off, stage + L.lds_off + i * (S::kWaves * 1024));
+__device__ __forceinline__ void copy_a(const TileLoader<S>& L, int kt, uint32_t dst, int i) {
+  copy16(L.a_buf, L.a_off[i], (uint32_t)kt * kRowB, dst + i * (kWaves * 1024));
 }
 template <class S>
-__device__ __forceinline__ void load_stage(const TileLoader<S>& L, int kt, uint32_t stage) {
-#pragma unroll
-  for (int i = 0; i < S::kCopies; ++i) load_copy<S>(L, kt, stage, i);
+__device__ __forceinline__ void copy_b(const TileLoader<S>& L, int kt, uint32_t dst, int i) {
+  copy16(L.b_buf, L.b_off[i], (uint32_t)kt * kRowB, dst + i * (kWaves * 1024));
 }
 
 template <int TT>
 struct Frags {
-  bf16x8_t a[2], b[TT];
+  bf16x8_t a[4], b[TT];
 };
 
-// fragment i of sub-step kk, in the order in which the MFMAs want them
+__device__ __forceinline__ bf16x8_t read16(int off) {
+  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<__attribute__((address_space(3))) const u32x4_t*>(
+                                          (lds_byte*)(uintptr_t)(uint32_t)off));
+}
+// fragment i of a half step, in the order in which the MFMAs want them; a_at, b_at: the lane's place in the stage
 template <int TT>
-__device__ __forceinline__ void read_frag(Frags<TT>& f, const uint8_t* stage, int a_off0, int b_off0, int kk, int i) {
-  if (i < 2)
-    f.a[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(stage + ((a_off0 ^ (kk << 5)) + i * 4096)));
-  else
-    f.b[i - 2] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(
-                                                  stage + kStageA + ((b_off0 ^ (kk << 5)) + (i - 2) * 4096)));
+__device__ __forceinline__ void read_frag(Frags<TT>& f, int a_at, int b_at, int i) {
+  if (i < 4) f.a[i] = read16(a_at + i * 16 * kRowB);
+  else f.b[i - 4] = read16(b_at + (i - 4) * 16 * kRowB);
 }
 
 // Wait until at most VM copies of this wave are in flight and every LDS read has returned, then a
@@ -155,354 +165,343 @@ __device__ __forceinline__ void wait_and_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// One reduction step: 4 sub-steps of 2*TT MFMAs.  On entry f0 holds the fragments of sub-step 0 of
-// stage `rd`.  Behind every MFMA stands at most one fragment read of the next sub-step and one copy
-// of the stage two steps ahead, in this order (a burst of copies would leave
-// the matrix unit idle while the address unit works it off).  The last sub-step holds
-// the step's barrier behind its first MFMA and reads the next stage's first fragments.
-template <class S, bool STEADY>   // STEADY: kt + 2 < n_kt is known, no conditions in the step
-__device__ __forceinline__ void step(f32x16_t (&acc)[2][S::TT], Frags<S::TT>& f0, Frags<S::TT>& f1,
-                                     const TileLoader<S>& L, int kt, int n_kt, const uint8_t* rd, uint32_t ld, const uint8_t* nx, int a_off0,
-                                     int b_off0) {
-  constexpr int TT = S::TT, kMfmas = 2 * TT, kCopies = S::kCopies;
-  const bool prefetch = STEADY || kt + 2 < n_kt;
-  const bool more = STEADY || kt + 1 < n_kt;
+// number of n things that stand in front of slot s, when they are spread over `percent` of the slots
+constexpr int placed(int s, int n, int slots, int percent) {
+  const int c = s * n * 100 / (slots * percent);
+  return s >= slots || c > n ? n : c;
+}
+
+// Half of a reduction step: 4*TT MFMAs on the fragments f, behind which, one by one, stand the reads of the next half's.
+// The second half starts with the step's barrier (behind four MFMAs): nobody reads stage kt any more, and stage kt+1
+// has landed.  Behind it stand the copies of x, in the first half those of W, in 60 % of the slots: with two heads x has
+// about one step to land, and one that is requested later holds everybody up (585 rows x 40 heads: W two steps ahead in the second half,
+// too, 107 us; W three and x two 96; W moved to the first half and x requested early 94).
+template <class S, bool SECOND, bool STEADY>   // STEADY: 0 < kt and the copies of this step are known to exist
+__device__ __forceinline__ void half_step(f32x4_t (&acc)[4][S::TT], Frags<S::TT>& f, Frags<S::TT>& f_next, const TileLoader<S>& L,
+                                          int kt, int n_kt, int a_at, int b_at, uint32_t ld) {
+  constexpr int kFirst = SECOND && S::kMfmas > 4 ? 4 : 0, kSlots = S::kMfmas - kFirst;
+  constexpr int kCopies = SECOND ? S::kBCopies : S::kACopies;
+  constexpr int kAhead = SECOND ? S::kBStages : S::kAStages - 1;
+  constexpr int kMost = S::kAStages > S::kBStages ? S::kAStages : S::kBStages;
+  const bool more = !SECOND || STEADY || kt + 1 < n_kt;
+  const bool copies = STEADY || (kt + kAhead < n_kt && (SECOND || kt > 0));   // kt = 0: W's places are full
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    Frags<TT>& f = kk & 1 ? f1 : f0;
-    Frags<TT>& f_next = kk & 1 ? f0 : f1;
+  for (int m = 0; m < S::kMfmas; ++m) {
+    if (SECOND && m == kFirst) {
+      if (STEADY || kt + kMost - 1 < n_kt) wait_and_barrier<S::in_flight()>();
+      else wait_and_barrier<0>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    acc[m & 3][m >> 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[m & 3], f.b[m >> 2], acc[m & 3][m >> 2], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (m >= kFirst) {
+      const int s = m - kFirst;
+      if (more) {
 #pragma unroll
-    for (int m = 0; m < kMfmas; ++m) {
-      acc[m & 1][m >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[m & 1], f.b[m >> 1], acc[m & 1][m >> 1], 0, 0, 0);
-      if (kk < 3) {
-        if (m < 2 + TT) read_frag<TT>(f_next, rd, a_off0, b_off0, kk + 1, m);
-        const int s = kk * kMfmas + m;
-        const int i = s * kCopies / (3 * kMfmas);
-        if (prefetch && (s + 1) * kCopies / (3 * kMfmas) > i) load_copy<S>(L, kt + 2, ld, i);
-      } else if (m == 0) {
-        // every read of stage rd has completed before any wave may overwrite it (next step), and the
-        // next stage has landed
-        if (prefetch) wait_and_barrier<kCopies>();
-        else wait_and_barrier<0>();
-        if (more && TT < 3) read_frag<TT>(f_next, nx, a_off0, b_off0, 0, 1 + TT);   // no slot left for it below
-      } else if (more && m - 1 < (TT < 3 ? 1 + TT : 2 + TT)) {
-        read_frag<TT>(f_next, nx, a_off0, b_off0, 0, m - 1);
+        for (int i = placed(s, S::kReads, kSlots, 100); i < placed(s + 1, S::kReads, kSlots, 100); ++i)
+          read_frag<S::TT>(f_next, a_at, b_at, i);
+      }
+      if (copies) {
+#pragma unroll
+        for (int i = placed(s, kCopies, kSlots, 60); i < placed(s + 1, kCopies, kSlots, 60); ++i) {
+          if (SECOND) copy_b<S>(L, kt + kAhead, ld, i);
+          else copy_a<S>(L, kt + kAhead, ld, i);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-// unit -> (channel tile, token tile).  Units are ordered so that 32 consecutive ones (what an
-// XCD's 32 CUs hold at a time) form 8 channel tiles x 4 token tiles: their W and x tiles
+// unit -> (pair of heads, token tile).  Units are ordered so that 32 consecutive ones (what an
+// XCD's 32 CUs hold at a time) form 8 pairs x 4 token tiles: their W and x tiles
 // together stream through that XCD's L2 once.
-__device__ __forceinline__ void unit_to_tile(const ProjTiles& pt, int unit, int& ch_tile, int& tok_tile) {
-  const int per_group = kTokGroup * pt.ch_tiles;
+__device__ __forceinline__ void unit_to_tile(const ProjTiles& pt, int unit, int& ch_pair, int& tok_tile) {
+  const int per_group = kTokGroup * pt.ch_pairs;
   const int full_groups = pt.tok_tiles / kTokGroup;
   int grp = unit / per_group;
   int gs = kTokGroup;
   if (grp >= full_groups) { grp = full_groups; gs = pt.tok_tiles - kTokGroup * full_groups; }
   const int local = unit - grp * per_group;
-  ch_tile = local / gs;
+  ch_pair = local / gs;
   tok_tile = kTokGroup * grp + local % gs;
 }
 
-template <class S, bool PER_HEAD>
-__global__ __attribute__((amdgpu_flat_work_group_size(S::kThreads, S::kThreads), amdgpu_waves_per_eu(S::kWaves / 4, S::kWaves / 4)))
-void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
-  constexpr int WT = S::WT, TT = S::TT, kWaves = S::kWaves, kThreads = S::kThreads;
-  constexpr int kTileTok = S::kTileTok, kWaveTok = S::kWaveTok, kStage = S::kStage, kCopies = S::kCopies;
-  constexpr int kAngBytes = kTileTok * kAngRowB;
-  // three stages of (W tile 16 KB, x tile 4*WT*TT KB); the epilogue reuses the space
-  constexpr int kLds = 3 * kStage;
-  static_assert(kAngBytes + 2 * kTileTok * (int)sizeof(float) <= kLds && kTileTok * kOutRowB <= kLds, "epilogue in LDS");
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
-  uint8_t* const lds0 = lds;
-  uint8_t* const lds1 = lds + kStage;
-  uint8_t* const lds2 = lds + 2 * kStage;
-  const uint32_t dst0 = LDS_ADDR(lds), dst1 = dst0 + kStage, dst2 = dst1 + kStage;   // the same, for the copies
+template <bool B>
+struct BoolTag {
+  static constexpr bool value = B;
+};
 
+// 16 channels of one token and two neighbouring 16-channel blocks c0, c1, as lane g of four holds them (channels
+// 4g .. 4g+3 of each): exchanged so that every lane has 8 neighbouring channels, 16*(c0 + g%2) + 8*(g/2) ..
+__device__ __forceinline__ uint4 join_quads(const uint32_t (&c0)[2], const uint32_t (&c1)[2]) {
+  const u32x2_t lo = __builtin_amdgcn_permlane16_swap(c0[0], c1[0], false, false);
+  const u32x2_t hi = __builtin_amdgcn_permlane16_swap(c0[1], c1[1], false, false);
+  return make_uint4(lo[0], hi[0], lo[1], hi[1]);
+}
+
+template <class S, bool PER_HEAD>
+__device__ __forceinline__ void project_tile(const ProjArgs& a, int ch_tile0, int tok0, uint8_t* lds) {
+  constexpr int TT = S::TT, kTileTok = S::kTileTok, kWaveTok = S::kWaveTok;
+  const int lds0 = (int)(uint32_t)(uintptr_t)(lds_byte*)lds;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 31, g = lane >> 5;
-  const int wc = wave & 1, wt = wave >> 1;   // channel half, token part of the tile
-
-  // Persistent work-groups, one per CU: a work-group walks its XCD's run of the unit list in
-  // strides of the XCD's CU count.  Not ending between tiles lets a tile's output stores drain
-  // under the next tile's reduction instead of holding up the hand-over of the CU.
-  for (int idx = (int)(blockIdx.x / kXcds); idx < pt.per_xcd; idx += pt.wgs_per_xcd) {
-  const int unit = (int)(blockIdx.x % kXcds) * pt.per_xcd + idx;
-  if (unit >= pt.total) break;   // wave-uniform; the whole work-group leaves together
-  int ch_tile, tok_tile;
-  unit_to_tile(pt, unit, ch_tile, tok_tile);
-  const int tok0 = tok_tile * kTileTok;
+  const int n = lane & 15, g = lane >> 4;
+  const int wq = wave % S::WC, wt = wave / S::WC;   // 64 channels of the tile, token part
+  const int wc = wq & 1, ch_tile = ch_tile0 + (wq >> 1);   // half of a head, which head
 
   TileLoader<S> L;
   {
-    const int l_row = lane >> 3, l_slot = lane & 7;
-    const int f = (lane >> 4) | ((wave & 1) << 2);
-    const uint32_t chunk_bytes = (uint32_t)((l_slot ^ f) * 16);
-    const int row = 8 * wave + l_row;
+    const int row = 8 * wave + (lane >> 3);
+    const uint32_t chunk_bytes = (uint32_t)(((lane & 7) ^ ((lane >> 4) | ((wave & 1) << 2))) * 16);
     const int64_t a_row_bytes = (int64_t)a.c_in * 2, b_row_bytes = a.x_tok * 2;
-    L.a_buf = raw_buffer(reinterpret_cast<const uint8_t*>(a.w) + (int64_t)ch_tile * kTileCh * a_row_bytes);
+    L.a_buf = raw_buffer(reinterpret_cast<const uint8_t*>(a.w) + (int64_t)ch_tile0 * kTileCh * a_row_bytes);
     L.b_buf = raw_buffer(reinterpret_cast<const uint8_t*>(a.x) + (int64_t)tok0 * b_row_bytes);
     const int last = a.n_tokens - 1 - tok0;   // >= 0
 #pragma unroll
-    for (int t = 0; t < S::kACopies; ++t) L.a_off[t] = (uint32_t)((row + 8 * kWaves * t) * a_row_bytes) + chunk_bytes;
+    for (int t = 0; t < S::kACopies; ++t) L.a_off[t] = (uint32_t)((row + 64 * t) * a_row_bytes) + chunk_bytes;
 #pragma unroll
-    for (int t = 0; t < 2 * TT; ++t) L.b_off[t] = (uint32_t)(min(row + 8 * kWaves * t, last) * b_row_bytes) + chunk_bytes;
-    L.lds_off = wave * 1024;
+    for (int t = 0; t < S::kBCopies; ++t)
+      L.b_off[t] = (uint32_t)(min(row + 64 * t, last) * b_row_bytes) + chunk_bytes;
   }
-  // fragment read offsets: row (64*wc or 32*TT*wt, + n), 16-byte chunk 2*kk + g -> slot ((2kk+g) ^ ((n>>1)&7))
-  const int fl = (n >> 1) & 7;
-  const int a_off0 = (64 * wc + n) * kRowB + ((g ^ fl) << 4);
-  const int b_off0 = (kWaveTok * wt + n) * kRowB + ((g ^ fl) << 4);
+  // fragment read offsets: row (64*wq or 16*TT*wt, + n), 16-byte chunk 4*half + g -> slot (4*half + g) ^ ((n>>1)&7)
+  const int slot = (g ^ (n >> 1)) << 4;
+  const int a_lane = lds0 + (64 * wq + n) * kRowB + slot;
+  const int b_lane = lds0 + S::kAStages * S::kStageA + (kWaveTok * wt + n) * kRowB + slot;
+  const uint32_t dst_a = (uint32_t)(lds0 + wave * 1024), dst_b = dst_a + S::kAStages * S::kStageA;
 
-  f32x16_t acc[2][TT];
+  f32x4_t acc[4][TT];
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[c][t][i] = 0.f;
+    for (int t = 0; t < TT; ++t) acc[c][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const int n_kt = a.c_in / kStepK;
   Frags<TT> f0, f1;
-  load_stage<S>(L, 0, dst0);
-  if (n_kt > 1) {
-    load_stage<S>(L, 1, dst1);
-    wait_and_barrier<kCopies>();
-  } else {
-    wait_and_barrier<0>();
-  }
+  constexpr int kMost = S::kAStages > S::kBStages ? S::kAStages : S::kBStages;
 #pragma unroll
-  for (int i = 0; i < 2 + TT; ++i) read_frag<TT>(f0, lds0, a_off0, b_off0, 0, i);
+  for (int j = 0; j < kMost; ++j) {
+    if (j < S::kAStages && j < n_kt) {
+#pragma unroll
+      for (int i = 0; i < S::kACopies; ++i) copy_a<S>(L, j, dst_a + j * S::kStageA, i);
+    }
+    if (j < S::kBStages && j < n_kt) {
+#pragma unroll
+      for (int i = 0; i < S::kBCopies; ++i) copy_b<S>(L, j, dst_b + j * S::kStageB, i);
+    }
+  }
+  if (n_kt >= kMost) wait_and_barrier<(S::kAStages - 1) * S::kACopies + (S::kBStages - 1) * S::kBCopies>();
+  else wait_and_barrier<0>();
+#pragma unroll
+  for (int i = 0; i < S::kReads; ++i) read_frag<TT>(f0, a_lane, b_lane, i);
   // lgkmcnt(0): enter the loop with nothing pending, so that the loop's own waits are counted
   // ones (a pending scalar load would make the compiler wait for every LDS read instead)
   __builtin_amdgcn_s_waitcnt(0xC07F);
-  int kt = 0;
-  for (; kt + 4 < n_kt; kt += 3) {   // steady state: every step prefetches two steps ahead
-    step<S, true>(acc, f0, f1, L, kt, n_kt, lds0, dst2, lds1, a_off0, b_off0);
-    step<S, true>(acc, f0, f1, L, kt + 1, n_kt, lds1, dst0, lds2, a_off0, b_off0);
-    step<S, true>(acc, f0, f1, L, kt + 2, n_kt, lds2, dst1, lds0, a_off0, b_off0);
-  }
-  for (; kt < n_kt; kt += 3) {       // the last (up to four) steps
-    step<S, false>(acc, f0, f1, L, kt, n_kt, lds0, dst2, lds1, a_off0, b_off0);
-    if (kt + 1 >= n_kt) break;
-    step<S, false>(acc, f0, f1, L, kt + 1, n_kt, lds1, dst0, lds2, a_off0, b_off0);
-    if (kt + 2 >= n_kt) break;
-    step<S, false>(acc, f0, f1, L, kt + 2, n_kt, lds2, dst1, lds0, a_off0, b_off0);
-  }
+  // stage kt's places; the lane's fragments stand there at a_lane, b_lane, those of the second half at an exclusive or of 64
+  int kt = 0, sa = 0, sb = 0;
+  auto one_step = [&](auto steady) {
+    constexpr bool kSteady = decltype(steady)::value;
+    const int sa_free = sa == 0 ? (S::kAStages - 1) * S::kStageA : sa - S::kStageA;
+    const int sa1 = sa == (S::kAStages - 1) * S::kStageA ? 0 : sa + S::kStageA;
+    const int sb1 = sb == (S::kBStages - 1) * S::kStageB ? 0 : sb + S::kStageB;
+    half_step<S, false, kSteady>(acc, f0, f1, L, kt, n_kt, (a_lane + sa) ^ 64, (b_lane + sb) ^ 64, dst_a + sa_free);
+    half_step<S, true, kSteady>(acc, f1, f0, L, kt, n_kt, a_lane + sa1, b_lane + sb1, dst_b + sb);
+    sa = sa1;
+    sb = sb1;
+    ++kt;
+  };
+  constexpr int kFarthest = S::kAStages - 1 > S::kBStages ? S::kAStages - 1 : S::kBStages;
+  one_step(BoolTag<false>{});
+  while (kt + kFarthest < n_kt) one_step(BoolTag<true>{});
+  while (kt < n_kt) one_step(BoolTag<false>{});   // the last steps
 
   // ------------------------------------------------------------------ epilogue
-  // acc[c][t][i]: token tok0 + 32*TT*wt + 32*t + n, channel 64*wc + 32*c + 8*(i/4) + 4*g + i%4 of the head.
-  // The closing barrier of the last step has passed: every wave is done with the stages.  The
-  // LDS now holds, in turn, the (cos, sin) rows of the tile's tokens (gathered with pairs
-  // on the lane axis, where a token's position is wave-uniform and its 64 pairs are three
-  // contiguous runs of the tables, then read back with tokens on the lane axis at constant
-  // offsets), the sums of squares, and the bf16 output tile, which leaves in whole 256-byte
-  // (token, head) rows.
-  uint8_t* const out_lds = lds;                                     // [tile tokens][kOutRowB]
-  uint8_t* const ang_lds = lds;                                     // [tile tokens][kAngRowB]: 64 x (cos, sin)
-  float* const ss_lds = reinterpret_cast<float*>(lds + kAngBytes);  // [wc][wt][t][32]
+  // acc[c][t][i]: token tok0 + kWaveTok*wt + 16*t + n, channel 64*wc + 16*c + 4*g + i of the head: two rotation pairs of
+  // one token.  The last step's barrier has passed: nobody reads or fills the stages any more.  (cos, sin) come straight
+  // from the tables, 16 bytes a lane: the four lanes of a token read 64 neighbouring bytes.  Outputs leave
+  // from registers, 16 bytes a lane.  All that crosses waves is the sum of squares of the other 64 channels.
+  float* const ss_lds = reinterpret_cast<float*>(lds);   // [wq][token of the tile]
   const int which = ch_tile / a.n_heads;   // 0: q, 1: k, 2: v
   const int head = ch_tile - which * a.n_heads;
-  // bias and gain of the lane's 32 channels: all loads issued together, ahead of their use
-  float4 gv[2][4];
-  if (which != 2) {
-    const float* gp = (which == 0 ? a.gain_q : a.gain_k) + head * kHeadDim + 64 * wc + 4 * g;
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) gv[c][b] = *reinterpret_cast<const float4*>(gp + 32 * c + 8 * b);
-  }
+  const int tok_lane = tok0 + kWaveTok * wt + n;
   if (a.bias) {
     const float* bp = a.bias + (int64_t)ch_tile * kTileCh + 64 * wc + 4 * g;
-    float4 bv[2][4];
+    f32x4_t bv[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 4; ++c) bv[c] = *reinterpret_cast<const f32x4_t*>(bp + 16 * c);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) bv[c][b] = *reinterpret_cast<const float4*>(bp + 32 * c + 8 * b);
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int t = 0; t < TT; ++t) {
-          acc[c][t][4 * b + 0] += bv[c][b].x; acc[c][t][4 * b + 1] += bv[c][b].y;
-          acc[c][t][4 * b + 2] += bv[c][b].z; acc[c][t][4 * b + 3] += bv[c][b].w;
-        }
+      for (int t = 0; t < TT; ++t) acc[c][t] += bv[c];
   }
-  uint32_t packed[TT][2][4][2];      // [t][c][b][pair of the 4 channels]
-  uint32_t packed_lo[TT][2][4][2];   // row-wide norm: bf16 of what the first rounding dropped
+  uint16_t* base;
+  int64_t tstride;
+  if (which == 0) { base = a.q_out + (int64_t)head * a.qo_head; tstride = a.qo_tok; }
+  else {
+    base = (which == 1 ? a.k_cache : a.v_cache) + a.dst_token * a.c_tok + (int64_t)head * a.c_head;
+    tstride = a.c_tok;
+  }
+  const int ch_store = 64 * wc + 16 * (g & 1) + 8 * (g >> 1);   // + 32 for the second two 16-channel blocks
+  auto store_token = [&](uint16_t* row, const uint32_t (&w)[4][2]) {
+#pragma unroll
+    for (int c = 0; c < 4; c += 2) *reinterpret_cast<uint4*>(row + ch_store + 16 * c) = join_quads(w[c], w[c + 1]);
+  };
 
   if (which == 2) {   // v: one rounding
+    wait_and_barrier<63>();   // the other waves' heads may be q's or k's
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
+    for (int t = 0; t < TT; ++t) {
+      const int token = tok_lane + 16 * t;
+      uint32_t w[4][2];
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          packed[t][c][b][0] = pack_bf16x2(acc[c][t][4 * b + 0], acc[c][t][4 * b + 1]);
-          packed[t][c][b][1] = pack_bf16x2(acc[c][t][4 * b + 2], acc[c][t][4 * b + 3]);
-        }
-  } else {
-    const int p_t = a.tl.pairs_t, p_h = a.tl.pairs_h, p_w = a.tl.pairs_w, p_th = p_t + p_h;
-    const float2* tab2 = reinterpret_cast<const float2*>(a.table);
-    // ---- gather: wave w fetches the rows of the tile's part w.  Positions are decoded
-    // with tokens on the lane axis; for the fetch the lane axis is the pair index (a token's
-    // 64 pairs are three contiguous runs of the tables) and token rr's table row offsets are
-    // broadcast from lane rr.  Lane j needs exactly one of the three offsets.
-    {
-      constexpr int kGather = kTileTok / kWaves, kBatch = kGather / 2;
-      const int last_tok = a.n_tokens - 1;
-      const int ig = a.token_offset + min(tok0 + kGather * wave + min(lane, kGather - 1), last_tok);   // past the end: last token's position
-      const int hw = a.grid_h * a.grid_w;
-      const int pf = ig / hw;
-      const int rem = ig - pf * hw;
-      const int ph = rem / a.grid_w;
-      const int pw = rem - ph * a.grid_w;
-      const int row_t = (a.start_frame + pf) * p_t, row_h = ph * p_h, row_w = pw * p_w;
-      const int j = lane;
-      const bool is_t = j < p_t, is_h = !is_t && j < p_th;
-      const int m_t = is_t ? -1 : 0, m_h = is_h ? -1 : 0, m_w = (is_t || is_h) ? 0 : -1;
-      const int cb = is_t ? (int)(a.tl.off_t / 2) + j
-                          : is_h ? (int)(a.tl.off_h / 2) + (j - p_t) : (int)(a.tl.off_w / 2) + (j - p_th);
-      uint8_t* dst = ang_lds + (kGather * wave) * kAngRowB + lane * 8;
-#pragma unroll
-      for (int b0 = 0; b0 < kGather; b0 += kBatch) {
-        float2 row[kBatch];
-#pragma unroll
-        for (int rr = 0; rr < kBatch; ++rr) {
-          const int st = __builtin_amdgcn_readlane(row_t, b0 + rr), sh = __builtin_amdgcn_readlane(row_h, b0 + rr),
-                    sw = __builtin_amdgcn_readlane(row_w, b0 + rr);
-          row[rr] = tab2[cb + ((st & m_t) | (sh & m_h) | (sw & m_w))];
-        }
-#pragma unroll
-        for (int rr = 0; rr < kBatch; ++rr) *reinterpret_cast<float2*>(dst + (b0 + rr) * kAngRowB) = row[rr];
+      for (int c = 0; c < 4; ++c) {
+        w[c][0] = pack_bf16x2(acc[c][t][0], acc[c][t][1]);
+        w[c][1] = pack_bf16x2(acc[c][t][2], acc[c][t][3]);
       }
+      // (the exchange between lanes stands outside the condition on the lane's token: all four lanes of a token agree)
+      if (token < a.n_tokens) store_token(base + (int64_t)token * tstride, w);
     }
-    // ---- sums of squares over the head: lane-local, the other half of the wave, the other wave
-    float tot[TT];
-    {
-      float ss[TT];
-#pragma unroll
-      for (int t = 0; t < TT; ++t) {
-        float sq = 0.f;
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) sq = fmaf(acc[c][t][i], acc[c][t][i], sq);
-        ss[t] = sum_across_halves(sq);
-      }
-      if (g == 0) {
-#pragma unroll
-        for (int t = 0; t < TT; ++t) ss_lds[((wc * WT + wt) * TT + t) * 32 + n] = ss[t];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int t = 0; t < TT; ++t)
-        tot[t] = ss_lds[((0 * WT + wt) * TT + t) * 32 + n] + ss_lds[((1 * WT + wt) * TT + t) * 32 + n];
-    }
-    float r[TT];
-    if (PER_HEAD) {
-#pragma unroll
-      for (int t = 0; t < TT; ++t) r[t] = 1.0f / sqrtf(tot[t] * (1.0f / kHeadDim) + a.eps);
-    } else {
-#pragma unroll
-      for (int t = 0; t < TT; ++t) r[t] = 1.0f;
-      if (wc == 0 && g == 0) {
-#pragma unroll
-        for (int t = 0; t < TT; ++t) {
-          const int token = tok0 + kWaveTok * wt + 32 * t + n;
-          if (token < a.n_tokens) a.sumsq[((int64_t)which * a.n_tokens + token) * a.n_heads + head] = tot[t];
-        }
-      }
-    }
-    // ---- normalise, gain, rotate; the lane's pairs are 32*wc + 2*g + (16*c + 4*b + e)
-    const uint8_t* ang_lane = ang_lds + (kWaveTok * wt + n) * kAngRowB + (32 * wc + 2 * g) * 8;
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-#pragma unroll
-        for (int t = 0; t < TT; ++t) {
-          const float4 cs = *reinterpret_cast<const float4*>(ang_lane + 32 * t * kAngRowB + (16 * c + 4 * b) * 8);
-          const float xa0 = acc[c][t][4 * b + 0] * r[t] * gv[c][b].x, xb0 = acc[c][t][4 * b + 1] * r[t] * gv[c][b].y;
-          const float xa1 = acc[c][t][4 * b + 2] * r[t] * gv[c][b].z, xb1 = acc[c][t][4 * b + 3] * r[t] * gv[c][b].w;
-          const float z0 = xa0 * cs.x - xb0 * cs.y, z1 = xa0 * cs.y + xb0 * cs.x;
-          const float z2 = xa1 * cs.z - xb1 * cs.w, z3 = xa1 * cs.w + xb1 * cs.z;
-          const uint32_t h0 = pack_bf16x2(z0, z1), h1 = pack_bf16x2(z2, z3);
-          packed[t][c][b][0] = h0;
-          packed[t][c][b][1] = h1;
-          if (!PER_HEAD) {
-            packed_lo[t][c][b][0] = pack_bf16x2(z0 - bf16_lo(h0), z1 - bf16_hi(h0));
-            packed_lo[t][c][b][1] = pack_bf16x2(z2 - bf16_lo(h1), z3 - bf16_hi(h1));
-          }
-        }
-      }
-    __syncthreads();   // every wave has read its angles: the output tile may overwrite them
+    return;
   }
 
-  // ---- the tile leaves in whole token rows: 16 lanes x 16 B = the 256 bytes of one (token, head)
+  const float* gp = (which == 0 ? a.gain_q : a.gain_k) + head * kHeadDim + 64 * wc + 4 * g;
+  f32x4_t gv[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) gv[c] = *reinterpret_cast<const f32x4_t*>(gp + 16 * c);
+
+  // The lane's pairs: 32*wc + 8*c + 2*g and the next one.  Table entry of pair j on each axis, as if j ran through that
+  // axis' row.  Where the two lie on different axes the second is fetched by itself.
+  const int p_t = a.tl.pairs_t, p_th = a.tl.pairs_t + a.tl.pairs_h;
+  const float2* tab2 = reinterpret_cast<const float2*>(a.table);
+  constexpr int kBatch = TT % 2 ? TT : TT / 2;
+  f32x4_t cs[kBatch][4];
+  auto fetch = [&](int t0) {
+    int bt[kBatch], bh[kBatch], bw[kBatch];
+#pragma unroll
+    for (int t = 0; t < kBatch; ++t) {   // tokens past the end: the last token's position
+      const uint32_t ig = (uint32_t)(a.token_offset + min(tok_lane + 16 * (t0 + t), a.n_tokens - 1));
+      const uint32_t f = fastdiv(ig, a.div_hw);
+      const uint32_t r = ig - f * a.div_hw.d;
+      const uint32_t ph = fastdiv(r, a.div_w);
+      const uint32_t pw = r - ph * a.div_w.d;
+      bt[t] = (int)(a.tl.off_t / 2) + (a.start_frame + (int)f) * a.tl.pairs_t;
+      bh[t] = (int)(a.tl.off_h / 2) + (int)ph * a.tl.pairs_h - p_t;
+      bw[t] = (int)(a.tl.off_w / 2) + (int)pw * a.tl.pairs_w - p_th;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int j = 32 * wc + 8 * c + 2 * g;
+      const bool on_t = j < p_t, on_h = j < p_th;
+#pragma unroll
+      for (int t = 0; t < kBatch; ++t)
+        __builtin_memcpy(&cs[t][c], tab2 + (uint32_t)(j + (on_t ? bt[t] : on_h ? bh[t] : bw[t])), 16);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int j = 32 * wc + 8 * c + 2 * g + 1;
+      const bool apart = j == p_t || j == p_th;
+      if (__builtin_amdgcn_ballot_w64(apart) != 0) {
+        const bool on_t = j < p_t, on_h = j < p_th;
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t) {
+          const float2 e = tab2[(uint32_t)(j + (on_t ? bt[t] : on_h ? bh[t] : bw[t]))];
+          if (apart) { cs[t][c][2] = e.x; cs[t][c][3] = e.y; }
+        }
+      }
+    }
+  };
+  fetch(0);
+
+  // ---- sums of squares over the head: lane-local, the other lanes of the token, the other wave
+  float tot[TT];
   {
-    uint8_t* out_lane = out_lds + (kWaveTok * wt + n) * kOutRowB + (64 * wc + 4 * g) * 2;
+    float ss[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      float sq = 0.f;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sq = fmaf(acc[c][t][i], acc[c][t][i], sq);
+      ss[t] = sum_across_rows(sq);
+    }
+    if (g == 0) {
+#pragma unroll
+      for (int t = 0; t < TT; ++t) ss_lds[wq * kTileTok + kWaveTok * wt + 16 * t + n] = ss[t];
+    }
+    wait_and_barrier<63>();   // the table rows stay in flight
 #pragma unroll
     for (int t = 0; t < TT; ++t)
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          *reinterpret_cast<uint2*>(out_lane + 32 * t * kOutRowB + (32 * c + 8 * b) * 2) =
-              make_uint2(packed[t][c][b][0], packed[t][c][b][1]);
+      tot[t] = ss_lds[(wq - wc) * kTileTok + kWaveTok * wt + 16 * t + n] + ss_lds[(wq - wc + 1) * kTileTok + kWaveTok * wt + 16 * t + n];
   }
-  __syncthreads();
-  {
-    uint16_t* base;
-    int64_t tstride;
-    if (which == 0) { base = a.q_out + (int64_t)head * a.qo_head; tstride = a.qo_tok; }
-    else {
-      base = (which == 1 ? a.k_cache : a.v_cache) + a.dst_token * a.c_tok + (int64_t)head * a.c_head;
-      tstride = a.c_tok;
-    }
-    const int chunk = tid & 15;
-#pragma unroll 8
-    for (int it = 0; it < kTileTok / (kThreads / 16); ++it) {
-      const int row = (tid >> 4) + (kThreads / 16) * it;
-      const int token = tok0 + row;
-      if (token < a.n_tokens)
-        *reinterpret_cast<uint4*>(base + (int64_t)token * tstride + chunk * 8) =
-            *reinterpret_cast<const uint4*>(out_lds + row * kOutRowB + chunk * 16);
+  float r[TT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t) r[t] = PER_HEAD ? 1.0f / sqrtf(tot[t] * (1.0f / kHeadDim) + a.eps) : 1.0f;
+  if (!PER_HEAD && wc == 0 && g == 0) {
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      const int token = tok_lane + 16 * t;
+      if (token < a.n_tokens) a.sumsq[((int64_t)which * a.n_tokens + token) * a.n_heads + head] = tot[t];
     }
   }
-  __syncthreads();   // the output tile has been read: the next tile's copies may overwrite it
-  if (!PER_HEAD && which != 2) {
-    // the low parts take the same way out, into the workspace rows [which][token][head][128]
-    uint8_t* out_lane = out_lds + (kWaveTok * wt + n) * kOutRowB + (64 * wc + 4 * g) * 2;
+  // ---- normalise, gain, rotate, store
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
+  for (int t0 = 0; t0 < TT; t0 += kBatch) {
+    if (t0) fetch(t0);
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+    for (int tb = 0; tb < kBatch; ++tb) {
+      const int t = t0 + tb, token = tok_lane + 16 * t;
+      uint32_t w[4][2], w_lo[4][2];   // w_lo: row-wide norm: bf16 of what the first rounding dropped
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-          *reinterpret_cast<uint2*>(out_lane + 32 * t * kOutRowB + (32 * c + 8 * b) * 2) =
-              make_uint2(packed_lo[t][c][b][0], packed_lo[t][c][b][1]);
-    __syncthreads();
-    uint16_t* base = a.resid + ((int64_t)which * a.n_tokens * a.n_heads + head) * kHeadDim;
-    const int64_t tstride = (int64_t)a.n_heads * kHeadDim;
-    const int chunk = tid & 15;
-#pragma unroll 8
-    for (int it = 0; it < kTileTok / (kThreads / 16); ++it) {
-      const int row = (tid >> 4) + (kThreads / 16) * it;
-      const int token = tok0 + row;
-      if (token < a.n_tokens)
-        *reinterpret_cast<uint4*>(base + (int64_t)token * tstride + chunk * 8) =
-            *reinterpret_cast<const uint4*>(out_lds + row * kOutRowB + chunk * 16);
+      for (int c = 0; c < 4; ++c) {
+        const f32x4_t e = cs[tb][c];
+        const float xa0 = acc[c][t][0] * r[t] * gv[c][0], xb0 = acc[c][t][1] * r[t] * gv[c][1];
+        const float xa1 = acc[c][t][2] * r[t] * gv[c][2], xb1 = acc[c][t][3] * r[t] * gv[c][3];
+        const float z0 = xa0 * e[0] - xb0 * e[1], z1 = xa0 * e[1] + xb0 * e[0];
+        const float z2 = xa1 * e[2] - xb1 * e[3], z3 = xa1 * e[3] + xb1 * e[2];
+        w[c][0] = pack_bf16x2(z0, z1);
+        w[c][1] = pack_bf16x2(z2, z3);
+        if (!PER_HEAD) {
+          w_lo[c][0] = pack_bf16x2(z0 - bf16_lo(w[c][0]), z1 - bf16_hi(w[c][0]));
+          w_lo[c][1] = pack_bf16x2(z2 - bf16_lo(w[c][1]), z3 - bf16_hi(w[c][1]));
+        }
+      }
+      if (token < a.n_tokens) {
+        store_token(base + (int64_t)token * tstride, w);
+        if (!PER_HEAD)   // workspace rows [which][token][head][128]
+          store_token(a.resid + (((int64_t)which * a.n_tokens + token) * a.n_heads + head) * kHeadDim, w_lo);
+      }
     }
-    __syncthreads();
   }
-  }   // next unit
+}
+
+template <int WC, int TOK, bool PER_HEAD>
+__device__ __forceinline__ void project_ragged(const ProjArgs& a, int ch_tile, int tok0, uint8_t* lds) {
+  constexpr int U = 16 * (kWaves / WC);   // the last tile of the tokens takes the narrowest body that holds them
+  const int left = a.n_tokens - tok0;
+  if (left <= 64) project_tile<Shape<WC, 64 / U>, PER_HEAD>(a, ch_tile, tok0, lds);
+  else if (left <= 128) project_tile<Shape<WC, 128 / U>, PER_HEAD>(a, ch_tile, tok0, lds);
+  else if (TOK > 192 && left <= 192) project_tile<Shape<WC, 192 / U>, PER_HEAD>(a, ch_tile, tok0, lds);
+  else project_tile<Shape<WC, TOK / U>, PER_HEAD>(a, ch_tile, tok0, lds);
+}
+
+template <int TOK, bool PER_HEAD>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(2, 2)))
+void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[160 * 1024];
+  const int idx = (int)(blockIdx.x / kXcds);
+  const bool pair = idx < pt.doubles;
+  const int local = pair ? idx : pt.doubles + (idx - pt.doubles) / 2;
+  const int unit = (int)(blockIdx.x % kXcds) * pt.per_xcd + local;
+  if (unit >= pt.total) return;   // the whole work-group leaves together
+  static_assert(Shape<4, TOK / 32>::kLds <= (int)sizeof(lds) && Shape<2, TOK / 64>::kLds <= (int)sizeof(lds), "LDS");
+  int ch_pair, tok_tile;
+  unit_to_tile(pt, unit, ch_pair, tok_tile);
+  const int tok0 = tok_tile * TOK;
+  const int ch_tile = 2 * ch_pair + (pair ? 0 : (idx - pt.doubles) & 1);
+  if (pair && ch_tile + 1 < pt.ch_tiles) project_ragged<4, TOK, PER_HEAD>(a, ch_tile, tok0, lds);
+  else if (ch_tile < pt.ch_tiles) project_ragged<2, TOK, PER_HEAD>(a, ch_tile, tok0, lds);
 }
 
 // Second pass of the row-wide norm: one wave per (tensor, token) sums the per-head sums of
@@ -546,55 +545,61 @@ size_t project_workspace_bytes(int n_tokens, int n_heads, bool per_head_norm) {
   return sumsq_bytes(n_tokens, n_heads) + (size_t)2 * n_tokens * n_heads * kHeadDim * sizeof(uint16_t);
 }
 
-template <class S>
-static ProjTiles make_tiles(int n_tokens, int n_heads) {
+// Two heads per work-group or one.  Two are cheaper per row, one fills the chip more evenly: whole rounds of doubles
+// first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles:
+// 4680 tokens x 12 heads, 342 pairs on 256 CUs, 84 / 91 / 98; 585 x 40, one round of doubles 108 / 123 / 108; 600 x 12, one round
+// of singles 31 / 31 / 45).
+constexpr double kSingleCost = 0.58;
+static ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
   ProjTiles pt;
   pt.ch_tiles = 3 * n_heads;
-  pt.tok_tiles = (n_tokens + S::kTileTok - 1) / S::kTileTok;
-  pt.total = pt.ch_tiles * pt.tok_tiles;
+  pt.ch_pairs = (pt.ch_tiles + 1) / 2;
+  pt.tok_tiles = (n_tokens + tile_tokens - 1) / tile_tokens;
+  pt.total = pt.ch_pairs * pt.tok_tiles;
   pt.per_xcd = (pt.total + kXcds - 1) / kXcds;
-  pt.wgs_per_xcd = pt.per_xcd < 32 ? pt.per_xcd : 32;
+  pt.doubles = 0;
+  double best = 1e30;
+  for (int r = 0; r <= (pt.per_xcd + kCusPerXcd - 1) / kCusPerXcd; ++r) {   // whole rounds of doubles, the rest in singles
+    const int d = r * kCusPerXcd < pt.per_xcd ? r * kCusPerXcd : pt.per_xcd;
+    const double cost = r + kSingleCost * ((2 * (pt.per_xcd - d) + kCusPerXcd - 1) / kCusPerXcd);
+    if (cost < best) { best = cost; pt.doubles = d; }
+  }
   return pt;
 }
-static int rounds(const ProjTiles& pt) { return (pt.per_xcd + pt.wgs_per_xcd - 1) / pt.wgs_per_xcd; }
 
-template <class S>
+template <int TOK>
 static void launch_tiles(const ProjArgs& a, hipStream_t st) {
-  const ProjTiles pt = make_tiles<S>(a.n_tokens, a.n_heads);
-  const dim3 grid(pt.wgs_per_xcd * kXcds), block(S::kThreads);
-  if (a.per_head_norm) hipLaunchKernelGGL((qkv_project_kernel<S, true>), grid, block, 0, st, a, pt);
-  else hipLaunchKernelGGL((qkv_project_kernel<S, false>), grid, block, 0, st, a, pt);
+  const ProjTiles pt = make_tiles(a.n_tokens, a.n_heads, TOK);
+  const dim3 grid((2 * pt.per_xcd - pt.doubles) * kXcds), block(kThreads);
+  if (a.per_head_norm) hipLaunchKernelGGL((qkv_project_kernel<TOK, true>), grid, block, 0, st, a, pt);
+  else hipLaunchKernelGGL((qkv_project_kernel<TOK, false>), grid, block, 0, st, a, pt);
 }
 
-// Two token widths of a tile.  256: two waves per SIMD, the cheaper one per row (18720 tokens x 12
-// heads: 336 us, 380 us in tiles of 192).  192: one wave per SIMD, for calls whose rounds of 256-wide
-// tiles over the 256 CUs end nearly empty or whose last tile is mostly padding.  A round of 192-wide
-// tiles takes 0.85 to 0.89 of a round of 256-wide ones where both take two rounds (585 rows x 120 channel
-// tiles: 108 against 122 us; 4680 x 15: 104 / 123; 1320 x 48 in half-filled rounds: 51 / 58) and 0.84 to
-// 0.98 where both take one (us, 192 / 256: 384 rows x 120 channel tiles, c_in 5120: 57 / 67; 600 x 36, 1536:
-// 29.4 / 30.7; 600 x 24, 1024: 17.1 / 17.4), so it is taken where its rounds at that price are cheaper.  At
-// short reductions the epilogue, which 8 waves work off faster, is most of a tile, and 256 is never the
-// slower one (us, 192 / 256: 600 x 6, c_in 256: 11.7 / 11.2; 600 x 9, 384: 12.4 / 12.2; equal at 512 and 640).
-// Tiles of 128 were never the fastest (122, 122, 61 us where the first three calls take 108, 104, 51).
-using Wide = Shape<4, 2>;
-using Mid = Shape<2, 3>;
+// Two token widths of a tile.  256 moves fewer bytes per product (18720 tokens x 12 heads 306 us, 317 in tiles of 192);
+// 192 is taken where its rounds of one-head tiles over the 256 CUs, at 0.88 of the price, are fewer: calls whose rounds of
+// 256-wide tiles end nearly empty or whose last tile is mostly padding (us, 192 / 256: 585 x 40 heads 108 / 130; 4680 x 5
+// heads 94 / 111; 2340 x 12 46 / 51; but 1560 x 12 40 / 35; 3000 x 24 179 / 165; 1000 x 40 99 / 86).
+// At reductions of at most 512 the epilogue is most of a tile and 192 has to take fewer rounds at full price.
 constexpr double kMidCost = 0.88;
 constexpr int kShortReduction = 512;
 
-template <class S>
-static int rounds(int n_tokens, int n_heads) { return rounds(make_tiles<S>(n_tokens, n_heads)); }
+// rounds of a tile per CU
+static int rounds(int n_tokens, int n_heads, int tile_tokens) {
+  const int total = 3 * n_heads * ((n_tokens + tile_tokens - 1) / tile_tokens);
+  return ((total + kXcds - 1) / kXcds + kCusPerXcd - 1) / kCusPerXcd;
+}
 
 int project_tile_tokens(int n_tokens, int n_heads, int c_in) {
   const double mid_cost = c_in <= kShortReduction ? 1.0 : kMidCost;
-  return rounds<Wide>(n_tokens, n_heads) <= rounds<Mid>(n_tokens, n_heads) * mid_cost ? Wide::kTileTok : Mid::kTileTok;
+  return rounds(n_tokens, n_heads, 256) <= rounds(n_tokens, n_heads, 192) * mid_cost ? 256 : 192;
 }
 
 hipError_t launch_project(const ProjArgs& a_in, hipStream_t st) {
   ProjArgs a = a_in;
   if (!a.per_head_norm)
     a.resid = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(a.sumsq) + sumsq_bytes(a.n_tokens, a.n_heads));
-  if (project_tile_tokens(a.n_tokens, a.n_heads, a.c_in) == Wide::kTileTok) launch_tiles<Wide>(a, st);
-  else launch_tiles<Mid>(a, st);
+  if (project_tile_tokens(a.n_tokens, a.n_heads, a.c_in) == 256) launch_tiles<256>(a, st);
+  else launch_tiles<192>(a, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.per_head_norm) return e;
   hipLaunchKernelGGL(scale_rows_kernel, dim3(2, (a.n_tokens + kScaleWaves - 1) / kScaleWaves),
