@@ -172,14 +172,16 @@ constexpr int placed(int s, int n, int slots, int percent) {
 }
 
 // Half of a reduction step: 4*TT MFMAs on the fragments f, behind which, one by one, stand the reads of the next half's.
-// The second half starts with the step's barrier (behind four MFMAs): nobody reads stage kt any more, and stage kt+1
-// has landed.  Behind it stand the copies of x, in the first half those of W, in 60 % of the slots: with two heads x has
-// about one step to land, and one that is requested later holds everybody up (585 rows x 40 heads: W two steps ahead in the second half,
-// too, 107 us; W three and x two 96; W moved to the first half and x requested early 94).
+// The second half starts with the step's barrier (behind eight MFMAs, four with one head): nobody reads stage kt any more, and
+// stage kt+1 has landed.  Behind it stand the copies of x, in the first half those of W, in the first 60 % (x of two heads 45 %)
+// of the slots: with two heads x has about one step to land, and one that is requested later, or waited for
+// earlier, holds everybody up (585 rows x 40 heads: W two steps ahead in the second half, too, 107 us; W three and x two 96; W
+// moved to the first half and x requested early 94; barrier behind 0, 4, 8, 12 MFMAs 104, 94, 92, 93).
 template <class S, bool SECOND, bool STEADY>   // STEADY: 0 < kt and the copies of this step are known to exist
 __device__ __forceinline__ void half_step(f32x4_t (&acc)[4][S::TT], Frags<S::TT>& f, Frags<S::TT>& f_next, const TileLoader<S>& L,
                                           int kt, int n_kt, int a_at, int b_at, uint32_t ld) {
-  constexpr int kFirst = SECOND && S::kMfmas > 4 ? 4 : 0, kSlots = S::kMfmas - kFirst;
+  constexpr int kFirst = !SECOND ? 0 : S::WC == 4 && S::kMfmas > 8 ? 8 : S::kMfmas > 4 ? 4 : 0;
+  constexpr int kSlots = S::kMfmas - kFirst, kPercent = SECOND && S::WC == 4 ? 45 : 60;
   constexpr int kCopies = SECOND ? S::kBCopies : S::kACopies;
   constexpr int kAhead = SECOND ? S::kBStages : S::kAStages - 1;
   constexpr int kMost = S::kAStages > S::kBStages ? S::kAStages : S::kBStages;
@@ -203,7 +205,7 @@ __device__ __forceinline__ void half_step(f32x4_t (&acc)[4][S::TT], Frags<S::TT>
       }
       if (copies) {
 #pragma unroll
-        for (int i = placed(s, kCopies, kSlots, 60); i < placed(s + 1, kCopies, kSlots, 60); ++i) {
+        for (int i = placed(s, kCopies, kSlots, kPercent); i < placed(s + 1, kCopies, kSlots, kPercent); ++i) {
           if (SECOND) copy_b<S>(L, kt + kAhead, ld, i);
           else copy_a<S>(L, kt + kAhead, ld, i);
         }
