@@ -28,7 +28,7 @@ MEASURED_TRAFFIC_BYTES = {
     "C4": {"chunk_attention": (162918.9 * 2.000 + 14261.4 * 1.000) * 1024,
            "crope_qk_norm_rotate_append": (21209.0 * 2.000 + 42175.7 * 1.000) * 1024,
            # profiles/qkv_project_C4_kernel_trace_and_counters.md (per-head norm variant)
-           "crope_qkv_project_norm_rotate_append": (76366.9 * 2.000 + 42120.0 * 1.000) * 1024},
+           "crope_qkv_project_norm_rotate_append": (69223.2 * 2.000 + 42120.1 * 1.000) * 1024},
 }
 
 

@@ -280,13 +280,11 @@ int32_t crope_qkv_project_tile_tokens(int32_t n_tokens, int32_t n_heads, int32_t
  * sum times 1/rms: one rounding of the fp32 value up to 2^-17 relative.
  *
  * Which path is faster (one MI355X, bf16, against a vendor GEMM followed by
- * crope_qk_norm_rotate_append): this call, with norm_group == 128, at widths of 1536 (12 heads x
- * 1728 tokens 28 against 31 us, x 18720 tokens 258 against 268; x 4680 tokens they tie, 76 to 80
- * against 77 to 80 on different boards).  It
- * is the slower one with the row-wide norm there (37, 94 and 326 against 31, 73 and 270 us: the
- * second pass and the workspace round trip) and at a width of 5120 (40 heads x 585 tokens 97
- * against 83 us, 5 heads x 4680 tokens 95 against 89).  Callers who want the fastest path at the large shapes
- * should use the two-kernel sequence.
+ * crope_qk_norm_rotate_append): this call, with norm_group == 128 (12 heads, c_in 1536 x 1728, 4680,
+ * 18720 tokens 25, 65 and 226 against 31, 76 and 271 us; c_in 5120, 40 heads x 585 tokens 79
+ * against 84, 5 heads x 4680 tokens 76 against 90).  It is the slower one with the row-wide norm (34, 83
+ * and 292 against 31, 73 and 272 us, 91 against 84, but 87 against 89): the second pass and the workspace
+ * round trip.  Callers who want the fastest path with that norm should use the two-kernel sequence.
  *
  *   x              device bf16 [n_tokens][c_in], row stride x_token_stride elements
  *   w_qkv          device bf16 [3*n_heads*128][c_in], contiguous ([out][in] like a linear layer)
