@@ -10,8 +10,8 @@
 // traffic for the rotation.
 //
 // A work-group is 8 waves of 64 channels x up to 128 tokens (v_mfma_f32_16x16x32_bf16, two waves per SIMD) and owns two
-// heads of q, k or v x 256 or 192 tokens, or one head; launch_project says which width when, make_tiles
-// how many of which.  What bounds the loop is the way from the L2 to LDS: with all CUs copying it carries 24 TB/s (39 bytes per
+// heads of q, k or v x 256 or 192 tokens, or one head; project_tiles.h says which
+// width when, and how many of which.  What bounds the loop is the way from the L2 to LDS: with all CUs copying it carries 24 TB/s (39 bytes per
 // clock and CU) in requests of 128 bytes and 13.5 TB/s in requests of 64, whatever the stride of the rows.  Hence two heads per
 // work-group (32 to 37 bytes per clock at full MFMA rate; one head 48 to 53), and reduction steps of 64, whose LDS
 // rows are one 128-byte request each (a version with steps of 32 and two work-groups per CU: 105 us where this takes 92).
@@ -30,6 +30,7 @@
 // workspace (16 mantissa bits together), so that the second pass rounds (hi + lo) / rms to
 // bf16 once: the stored result is the single rounding of the fp32 value up to 2^-17 relative.
 #include "crope_internal.h"
+#include "project_tiles.h"
 
 namespace crope {
 namespace {
@@ -61,13 +62,6 @@ constexpr int kTileCh = 128;    // one head
 constexpr int kStepK = 64;      // reduction elements per LDS stage
 constexpr int kRowB = kStepK * 2;             // 128 B per LDS row
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
-constexpr int kXcds = 8, kCusPerXcd = 32;
-constexpr int kTokGroup = 4;    // token tiles walked together with 8 pairs of heads by one XCD's CUs
-
-// Units of work, per XCD a run of (pair of heads, token tile): the first `doubles` are one work-group's each, the others two's.
-struct ProjTiles {
-  int ch_tiles, ch_pairs, tok_tiles, total, per_xcd, doubles;
-};
 
 // A tile of 64*WC channels (one head or two) x 16*TT*(8/WC) tokens: 8 waves of 64 channels x 16*TT tokens.
 template <int WC_, int TT_>
@@ -213,20 +207,6 @@ __device__ __forceinline__ void half_step(f32x4_t (&acc)[4][S::TT], Frags<S::TT>
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-}
-
-// unit -> (pair of heads, token tile).  Units are ordered so that 32 consecutive ones (what an
-// XCD's 32 CUs hold at a time) form 8 pairs x 4 token tiles: their W and x tiles
-// together stream through that XCD's L2 once.
-__device__ __forceinline__ void unit_to_tile(const ProjTiles& pt, int unit, int& ch_pair, int& tok_tile) {
-  const int per_group = kTokGroup * pt.ch_pairs;
-  const int full_groups = pt.tok_tiles / kTokGroup;
-  int grp = unit / per_group;
-  int gs = kTokGroup;
-  if (grp >= full_groups) { grp = full_groups; gs = pt.tok_tiles - kTokGroup * full_groups; }
-  const int local = unit - grp * per_group;
-  ch_pair = local / gs;
-  tok_tile = kTokGroup * grp + local % gs;
 }
 
 template <bool B>
@@ -492,18 +472,13 @@ template <int TOK, bool PER_HEAD>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(2, 2)))
 void qkv_project_kernel(ProjArgs a, ProjTiles pt) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[160 * 1024];
-  const int idx = (int)(blockIdx.x / kXcds);
-  const bool pair = idx < pt.doubles;
-  const int local = pair ? idx : pt.doubles + (idx - pt.doubles) / 2;
-  const int unit = (int)(blockIdx.x % kXcds) * pt.per_xcd + local;
-  if (unit >= pt.total) return;   // the whole work-group leaves together
+  const ProjWork w = project_work(pt, blockIdx.x);
+  if (w.heads == 0) return;   // the whole work-group leaves together
   static_assert(Shape<4, TOK / 32>::kLds <= (int)sizeof(lds) && Shape<2, TOK / 64>::kLds <= (int)sizeof(lds), "LDS");
-  int ch_pair, tok_tile;
-  unit_to_tile(pt, unit, ch_pair, tok_tile);
-  const int tok0 = tok_tile * TOK;
-  const int ch_tile = 2 * ch_pair + (pair ? 0 : (idx - pt.doubles) & 1);
-  if (pair && ch_tile + 1 < pt.ch_tiles) project_ragged<4, TOK, PER_HEAD>(a, ch_tile, tok0, lds);
-  else if (ch_tile < pt.ch_tiles) project_ragged<2, TOK, PER_HEAD>(a, ch_tile, tok0, lds);
+  // (without readfirstlane the compiler works the tile out again in every body)
+  const int ch_tile = __builtin_amdgcn_readfirstlane(w.ch_tile), tok0 = __builtin_amdgcn_readfirstlane(w.tok_tile * TOK);
+  if (w.heads == 2) project_ragged<4, TOK, PER_HEAD>(a, ch_tile, tok0, lds);
+  else project_ragged<2, TOK, PER_HEAD>(a, ch_tile, tok0, lds);
 }
 
 // Second pass of the row-wide norm: one wave per (tensor, token) sums the per-head sums of
@@ -547,54 +522,15 @@ size_t project_workspace_bytes(int n_tokens, int n_heads, bool per_head_norm) {
   return sumsq_bytes(n_tokens, n_heads) + (size_t)2 * n_tokens * n_heads * kHeadDim * sizeof(uint16_t);
 }
 
-// Two heads per work-group or one.  Two are cheaper per row, one fills the chip more evenly: whole rounds of doubles
-// first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles:
-// 4680 tokens x 12 heads, 342 pairs on 256 CUs, 84 / 91 / 98; 585 x 40, one round of doubles 108 / 123 / 108; 600 x 12, one round
-// of singles 31 / 31 / 45).
-constexpr double kSingleCost = 0.58;
-static ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
-  ProjTiles pt;
-  pt.ch_tiles = 3 * n_heads;
-  pt.ch_pairs = (pt.ch_tiles + 1) / 2;
-  pt.tok_tiles = (n_tokens + tile_tokens - 1) / tile_tokens;
-  pt.total = pt.ch_pairs * pt.tok_tiles;
-  pt.per_xcd = (pt.total + kXcds - 1) / kXcds;
-  pt.doubles = 0;
-  double best = 1e30;
-  for (int r = 0; r <= (pt.per_xcd + kCusPerXcd - 1) / kCusPerXcd; ++r) {   // whole rounds of doubles, the rest in singles
-    const int d = r * kCusPerXcd < pt.per_xcd ? r * kCusPerXcd : pt.per_xcd;
-    const double cost = r + kSingleCost * ((2 * (pt.per_xcd - d) + kCusPerXcd - 1) / kCusPerXcd);
-    if (cost < best) { best = cost; pt.doubles = d; }
-  }
-  return pt;
-}
-
 template <int TOK>
 static void launch_tiles(const ProjArgs& a, hipStream_t st) {
   const ProjTiles pt = make_tiles(a.n_tokens, a.n_heads, TOK);
-  const dim3 grid((2 * pt.per_xcd - pt.doubles) * kXcds), block(kThreads);
+  const dim3 grid(project_blocks(pt)), block(kThreads);
   if (a.per_head_norm) hipLaunchKernelGGL((qkv_project_kernel<TOK, true>), grid, block, 0, st, a, pt);
   else hipLaunchKernelGGL((qkv_project_kernel<TOK, false>), grid, block, 0, st, a, pt);
 }
 
-// Two token widths of a tile.  256 moves fewer bytes per product (18720 tokens x 12 heads 306 us, 317 in tiles of 192);
-// 192 is taken where its rounds of one-head tiles over the 256 CUs, at 0.88 of the price, are fewer: calls whose rounds of
-// 256-wide tiles end nearly empty or whose last tile is mostly padding (us, 192 / 256: 585 x 40 heads 108 / 130; 4680 x 5
-// heads 94 / 111; 2340 x 12 46 / 51; but 1560 x 12 40 / 35; 3000 x 24 179 / 165; 1000 x 40 99 / 86).
-// At reductions of at most 512 the epilogue is most of a tile and 192 has to take fewer rounds at full price.
-constexpr double kMidCost = 0.88;
-constexpr int kShortReduction = 512;
-
-// rounds of a tile per CU
-static int rounds(int n_tokens, int n_heads, int tile_tokens) {
-  const int total = 3 * n_heads * ((n_tokens + tile_tokens - 1) / tile_tokens);
-  return ((total + kXcds - 1) / kXcds + kCusPerXcd - 1) / kCusPerXcd;
-}
-
-int project_tile_tokens(int n_tokens, int n_heads, int c_in) {
-  const double mid_cost = c_in <= kShortReduction ? 1.0 : kMidCost;
-  return rounds(n_tokens, n_heads, 256) <= rounds(n_tokens, n_heads, 192) * mid_cost ? 256 : 192;
-}
+int project_tile_tokens(int n_tokens, int n_heads, int c_in) { return project_tile_width(n_tokens, n_heads, c_in); }
 
 hipError_t launch_project(const ProjArgs& a_in, hipStream_t st) {
   ProjArgs a = a_in;

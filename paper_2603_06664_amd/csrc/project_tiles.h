@@ -1,0 +1,126 @@
+// Work division of the projection: which work-group computes which tiles.  Host and device use the same code, and nothing
+// here needs a GPU.
+#pragma once
+#include "fastdiv.h"
+
+namespace crope {
+
+constexpr int kProjXcds = 8, kProjCusPerXcd = 32;
+constexpr int kTokGroup = 4;    // token tiles walked together with 8 pairs of heads by one XCD's CUs
+
+// The output as tiles of one head of q, k or v ("channel tile") x tile_tokens tokens.  Two neighbouring channel tiles make a unit; v
+// starts at an even one, so that no unit holds k and v; an odd last one (odd numbers of heads) is a unit by itself.  Four
+// token tiles make a group, whose units are walked channels first, tokens within: 32 consecutive ones (what an
+// XCD's 32 CUs hold at a time) are 8 pairs x 4 token tiles, whose W and x tiles stream through that XCD's L2 once.
+// With `doubles`, every XCD has a run of units: the first `doubles` are one work-group's each, the others two's (of which the one
+// for the missing tile of an odd unit leaves at once).  Without, every XCD has a run of tiles, one work-group's each: runs of
+// units gave 4346 tokens x 5 heads, c_in 4608, 255 tiles, more than 256 work-groups and so pairs, 99 us; 74 in one round.
+struct ProjTiles {
+  int ch_tiles, tok_tiles, doubles;
+  int total, per_xcd;   // units, or tiles without doubles
+  FastDiv div_group;    // by those of a group
+};
+
+// What a work-group computes: `heads` (0, 1 or 2) neighbouring channel tiles from ch_tile on, of one token tile.
+struct ProjWork {
+  int heads, ch_tile, tok_tile;
+};
+
+CROPE_HD inline ProjWork project_work(const ProjTiles& pt, uint32_t block) {   // without branches: everything is loaded at once
+  const int idx = (int)(block / kProjXcds), rest = idx - pt.doubles;
+  const bool two = rest < 0, tiles = pt.doubles == 0;
+  const int at = (int)(block % kProjXcds) * pt.per_xcd + (two || tiles ? idx : pt.doubles + (rest >> 1));
+  const int group = (int)fastdiv((uint32_t)at, pt.div_group), local = at - group * (int)pt.div_group.d;
+  const int left = pt.tok_tiles - kTokGroup * group, gs = left >= kTokGroup ? kTokGroup : left > 1 ? left : 1;
+  const int in_pairs = gs * (pt.ch_tiles / 2);
+  const bool paired = local < 2 * in_pairs;   // tiles: not an odd last one
+  const int unit = !tiles ? local : paired ? local >> 1 : local - in_pairs;
+  const int half = two ? 0 : !tiles ? rest & 1 : paired ? local & 1 : 0;
+  const int pair = (int)((uint32_t)unit * (gs == 3 ? 21846u : 65536u >> (gs >> 1)) >> 16);   // unit / gs, unit < 32768
+  const int ch_tile = 2 * pair + half;
+  const int most = two ? 2 : 1, have = at < pt.total ? pt.ch_tiles - ch_tile : 0;
+  return ProjWork{have < most ? have : most, ch_tile, kTokGroup * group + unit - pair * gs};
+}
+
+// Work-groups of the launch.
+inline int project_blocks(const ProjTiles& pt) {
+  return (pt.doubles ? 2 * pt.per_xcd - pt.doubles : pt.per_xcd) * kProjXcds;
+}
+
+// A one-head work-group's time in two-head ones.
+constexpr double kSingleCost = 0.58;
+
+// Time of an XCD's doubles and singles in doubles, when its CUs take the doubles first.
+inline double project_span(int doubles, int singles) {
+  const int late = doubles % kProjCusPerXcd;   // CUs that are a double behind the others
+  double t0 = doubles / kProjCusPerXcd, t1 = t0 + 1.0, end = late ? t1 : t0;
+  while (singles > 0) {
+    double& t = late == 0 || t0 <= t1 ? t0 : t1;
+    const int cus = &t == &t0 ? kProjCusPerXcd - late : late;
+    const int waves = late == 0 ? (singles + cus - 1) / cus : 1;
+    singles -= waves * cus;
+    t += waves * kSingleCost;
+    end = t > end ? t : end;
+  }
+  return end;
+}
+
+// Two heads per work-group or one.  Two are cheaper per row, one fills the chip more evenly: whole rounds of doubles
+// first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles:
+// 4680 tokens x 12 heads, 342 pairs on 256 CUs, 84 / 91 / 98; 585 x 40, one round of doubles 108 / 123 / 108; 600 x 12, one round
+// of singles 31 / 31 / 45).  An odd unit is one tile.  Equal estimates: as many whole rounds as possible, which move fewer
+// bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33 units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads:
+// 0.2 % behind the fastest of all numbers of rounds on average, 11 % at worst; counted as two tiles, the odd unit made that 1.5 and 43.
+inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
+  ProjTiles pt;
+  pt.ch_tiles = 3 * n_heads;
+  pt.tok_tiles = (n_tokens + tile_tokens - 1) / tile_tokens;
+  const int ch_pairs = pt.ch_tiles / 2, ch_units = pt.ch_tiles - ch_pairs, odd = ch_units - ch_pairs;
+  const int all = ch_units * pt.tok_tiles, units = (all + kProjXcds - 1) / kProjXcds;   // per XCD
+  const int tiles = (pt.ch_tiles * pt.tok_tiles + 2 * kProjXcds - 1) / (2 * kProjXcds) * 2;   // even: no pair is cut
+  auto odd_before = [&](int unit) {   // units of one tile before this one
+    if (!odd) return 0;
+    const int group = unit / (kTokGroup * ch_units), local = unit - group * kTokGroup * ch_units;
+    const int left = pt.tok_tiles - kTokGroup * group, in_pairs = (left < kTokGroup ? left : kTokGroup) * ch_pairs;
+    return group * kTokGroup + (local > in_pairs ? local - in_pairs : 0);
+  };
+  pt.doubles = 0;
+  double best = project_span(0, tiles);
+  for (int r = 1; r <= (units + kProjCusPerXcd - 1) / kProjCusPerXcd; ++r) {   // whole rounds of doubles, the rest in singles
+    const int d = r * kProjCusPerXcd < units ? r * kProjCusPerXcd : units;
+    double cost = 0.0;
+    for (int x = 0; x < (odd ? kProjXcds : 1); ++x) {   // the slowest run; without odd units the first one
+      const int u0 = x * units, u1 = u0 + units < all ? u0 + units : all, u = u0 + d < u1 ? u0 + d : u1;
+      if (u0 >= u1) break;
+      const int lone = odd_before(u) - odd_before(u0), lone_rest = odd_before(u1) - odd_before(u);
+      const double c = project_span(u - u0 - lone, lone + 2 * (u1 - u) - lone_rest);
+      cost = c > cost ? c : cost;
+    }
+    if (cost < best - 1e-9 || (d % kProjCusPerXcd == 0 && cost < best + 1e-9)) { best = cost; pt.doubles = d; }
+  }
+  pt.total = (pt.doubles ? ch_units : pt.ch_tiles) * pt.tok_tiles;
+  pt.per_xcd = pt.doubles ? units : tiles;
+  pt.div_group = make_fastdiv((uint32_t)(kTokGroup * (pt.doubles ? ch_units : pt.ch_tiles)));
+  return pt;
+}
+
+// Two token widths of a tile.  256 moves fewer bytes per product (18720 tokens x 12 heads 306 us, 317 in tiles of 192);
+// 192 is taken where its rounds of one-head tiles over the 256 CUs, at 0.88 of the price, are fewer: calls whose rounds of
+// 256-wide tiles end nearly empty or whose last tile is mostly padding (us, 192 / 256: 585 x 40 heads 108 / 130; 4680 x 5
+// heads 94 / 111; 2340 x 12 46 / 51; but 1560 x 12 40 / 35; 3000 x 24 179 / 165; 1000 x 40 99 / 86).
+// At reductions of at most 512 the epilogue is most of a tile and 192 has to take fewer rounds at full price.
+constexpr double kMidCost = 0.88;
+constexpr int kShortReduction = 512;
+
+// rounds of a tile per CU
+inline int project_rounds(int n_tokens, int n_heads, int tile_tokens) {
+  const int total = 3 * n_heads * ((n_tokens + tile_tokens - 1) / tile_tokens);
+  return ((total + kProjXcds - 1) / kProjXcds + kProjCusPerXcd - 1) / kProjCusPerXcd;
+}
+
+inline int project_tile_width(int n_tokens, int n_heads, int c_in) {
+  const double mid_cost = c_in <= kShortReduction ? 1.0 : kMidCost;
+  return project_rounds(n_tokens, n_heads, 256) <= project_rounds(n_tokens, n_heads, 192) * mid_cost ? 256 : 192;
+}
+
+}  // namespace crope
