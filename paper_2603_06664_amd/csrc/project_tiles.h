@@ -8,17 +8,18 @@ namespace crope {
 constexpr int kProjXcds = 8, kProjCusPerXcd = 32;
 constexpr int kTokGroup = 4;    // token tiles walked together with 8 pairs of heads by one XCD's CUs
 
-// The output as tiles of one head of q, k or v ("channel tile") x tile_tokens tokens.  Two neighbouring channel tiles make a unit; v
-// starts at an even one, so that no unit holds k and v; an odd last one (odd numbers of heads) is a unit by itself.  Four
-// token tiles make a group, whose units are walked channels first, tokens within: 32 consecutive ones (what an
-// XCD's 32 CUs hold at a time) are 8 pairs x 4 token tiles, whose W and x tiles stream through that XCD's L2 once.
-// With `doubles`, every XCD has a run of units: the first `doubles` are one work-group's each, the others two's (of which the one
-// for the missing tile of an odd unit leaves at once).  Without, every XCD has a run of tiles, one work-group's each: runs of
-// units gave 4346 tokens x 5 heads, c_in 4608, 255 tiles, more than 256 work-groups and so pairs, 99 us; 74 in one round.
+// The output as tiles of one head of q, k or v ("channel tile") x tile_tokens tokens.  Four token tiles make a group, walked channels
+// first, tokens within: 32 consecutive units (what an XCD's 32 CUs hold at a time) are 8 x 4 of them, whose W and x tiles
+// stream through that XCD's L2 once; every XCD has a run of units.  With `doubles`, a unit is two neighbouring channel tiles; v
+// starts at an even one, so that no unit holds k and v, and the odd last one (odd numbers of heads) is one tile.  The first
+// `doubles` units of a run are one work-group's each, the others two's (of which the one for a missing tile leaves at once).
+// Without, a unit is one tile: units of two gave 4346 tokens x 5 heads, c_in 4608, 255 tiles, more than 256 work-groups and
+// so doubles, 99 us; 74 in one round.
 struct ProjTiles {
-  int ch_tiles, tok_tiles, doubles;
-  int total, per_xcd;   // units, or tiles without doubles
-  FastDiv div_group;    // by those of a group
+  int ch_tiles, tok_tiles;
+  int total, per_xcd, doubles;   // units
+  int pairs;                     // 1: units of two tiles, 0: of one
+  FastDiv div_group;             // by the units of a group
 };
 
 // What a work-group computes: `heads` (0, 1 or 2) neighbouring channel tiles from ch_tile on, of one token tile.
@@ -26,25 +27,23 @@ struct ProjWork {
   int heads, ch_tile, tok_tile;
 };
 
-CROPE_HD inline ProjWork project_work(const ProjTiles& pt, uint32_t block) {   // without branches: everything is loaded at once
+CROPE_HD inline ProjWork project_work(const ProjTiles& pt, uint32_t block) {
   const int idx = (int)(block / kProjXcds), rest = idx - pt.doubles;
-  const bool two = rest < 0, tiles = pt.doubles == 0;
-  const int at = (int)(block % kProjXcds) * pt.per_xcd + (two || tiles ? idx : pt.doubles + (rest >> 1));
-  const int group = (int)fastdiv((uint32_t)at, pt.div_group), local = at - group * (int)pt.div_group.d;
+  const bool first = rest < 0;   // a whole unit
+  const int unit = (int)(block % kProjXcds) * pt.per_xcd + (first ? idx : pt.doubles + (rest >> pt.pairs));
+  const int group = (int)fastdiv((uint32_t)unit, pt.div_group), local = unit - group * (int)pt.div_group.d;
   const int left = pt.tok_tiles - kTokGroup * group, gs = left >= kTokGroup ? kTokGroup : left > 1 ? left : 1;
-  const int in_pairs = gs * (pt.ch_tiles / 2);
-  const bool paired = local < 2 * in_pairs;   // tiles: not an odd last one
-  const int unit = !tiles ? local : paired ? local >> 1 : local - in_pairs;
-  const int half = two ? 0 : !tiles ? rest & 1 : paired ? local & 1 : 0;
-  const int pair = (int)((uint32_t)unit * (gs == 3 ? 21846u : 65536u >> (gs >> 1)) >> 16);   // unit / gs, unit < 32768
-  const int ch_tile = 2 * pair + half;
-  const int most = two ? 2 : 1, have = at < pt.total ? pt.ch_tiles - ch_tile : 0;
-  return ProjWork{have < most ? have : most, ch_tile, kTokGroup * group + unit - pair * gs};
+  const int ch = (int)((uint32_t)local * (gs == 3 ? 21846u : 65536u >> (gs >> 1)) >> 16);   // local / gs, local < 32768
+  const int ch_tile = (ch << pt.pairs) + (first ? 0 : rest & pt.pairs);
+  ProjWork w{1, ch_tile, kTokGroup * group + local - ch * gs};
+  if (first && ch_tile + 1 < pt.ch_tiles) w.heads = 2;
+  if (unit >= pt.total || ch_tile >= pt.ch_tiles) w.heads = 0;
+  return w;
 }
 
 // Work-groups of the launch.
 inline int project_blocks(const ProjTiles& pt) {
-  return (pt.doubles ? 2 * pt.per_xcd - pt.doubles : pt.per_xcd) * kProjXcds;
+  return (pt.doubles + ((pt.per_xcd - pt.doubles) << pt.pairs)) * kProjXcds;
 }
 
 // A one-head work-group's time in two-head ones.
@@ -68,16 +67,16 @@ inline double project_span(int doubles, int singles) {
 // Two heads per work-group or one.  Two are cheaper per row, one fills the chip more evenly: whole rounds of doubles
 // first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles:
 // 4680 tokens x 12 heads, 342 pairs on 256 CUs, 84 / 91 / 98; 585 x 40, one round of doubles 108 / 123 / 108; 600 x 12, one round
-// of singles 31 / 31 / 45).  An odd unit is one tile.  Equal estimates: as many whole rounds as possible, which move fewer
+// of singles 31 / 31 / 45).  An odd last tile is one tile, not two.  Equal estimates: as many whole rounds as possible, which move fewer
 // bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33 units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads:
-// 0.2 % behind the fastest of all numbers of rounds on average, 11 % at worst; counted as two tiles, the odd unit made that 1.5 and 43.
+// 0.2 % behind the fastest of all numbers of rounds on average, 11 % at worst; counted as two, it made that 1.5 and 43.
 inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
   ProjTiles pt;
   pt.ch_tiles = 3 * n_heads;
   pt.tok_tiles = (n_tokens + tile_tokens - 1) / tile_tokens;
   const int ch_pairs = pt.ch_tiles / 2, ch_units = pt.ch_tiles - ch_pairs, odd = ch_units - ch_pairs;
   const int all = ch_units * pt.tok_tiles, units = (all + kProjXcds - 1) / kProjXcds;   // per XCD
-  const int tiles = (pt.ch_tiles * pt.tok_tiles + 2 * kProjXcds - 1) / (2 * kProjXcds) * 2;   // even: no pair is cut
+  const int tiles = (pt.ch_tiles * pt.tok_tiles + kProjXcds - 1) / kProjXcds;
   auto odd_before = [&](int unit) {   // units of one tile before this one
     if (!odd) return 0;
     const int group = unit / (kTokGroup * ch_units), local = unit - group * kTokGroup * ch_units;
@@ -98,9 +97,10 @@ inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
     }
     if (cost < best - 1e-9 || (d % kProjCusPerXcd == 0 && cost < best + 1e-9)) { best = cost; pt.doubles = d; }
   }
-  pt.total = (pt.doubles ? ch_units : pt.ch_tiles) * pt.tok_tiles;
-  pt.per_xcd = pt.doubles ? units : tiles;
-  pt.div_group = make_fastdiv((uint32_t)(kTokGroup * (pt.doubles ? ch_units : pt.ch_tiles)));
+  pt.pairs = pt.doubles > 0;
+  pt.total = pt.pairs ? all : pt.ch_tiles * pt.tok_tiles;
+  pt.per_xcd = pt.pairs ? units : tiles;
+  pt.div_group = make_fastdiv((uint32_t)(kTokGroup * (pt.pairs ? ch_units : pt.ch_tiles)));
   return pt;
 }
 
