@@ -330,8 +330,9 @@ __device__ __forceinline__ void project_tile(const ProjArgs& a, int ch_tile0, in
     for (int c = 0; c < 4; c += 2) *reinterpret_cast<uint4*>(row + ch_store + 16 * c) = join_quads(w[c], w[c + 1]);
   };
 
-  if (which == 2) {   // v: one rounding
-    wait_and_barrier<63>();   // the other waves' heads may be q's or k's
+  // v: one rounding.  No LDS, so no barrier: all waves of the work-group are here, since v starts at channel tile 2*n_heads, an even
+  // one, and pairs of heads start at even ones, so that none holds k and v.
+  if (which == 2) {
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
       const int token = tok_lane + 16 * t;
@@ -341,7 +342,7 @@ __device__ __forceinline__ void project_tile(const ProjArgs& a, int ch_tile0, in
         w[c][0] = pack_bf16x2(acc[c][t][0], acc[c][t][1]);
         w[c][1] = pack_bf16x2(acc[c][t][2], acc[c][t][3]);
       }
-      // (the exchange between lanes stands outside the condition on the lane's token: all four lanes of a token agree)
+      // (store_token's exchange between lanes stands inside the condition: the four lanes that exchange have the same token)
       if (token < a.n_tokens) store_token(base + (int64_t)token * tstride, w);
     }
     return;

@@ -68,6 +68,8 @@ def test_every_tile_once(works, n, heads, width):
         for c in range(ch, ch + k):
             seen[c, tok] += 1
     assert (seen == 1).all()
+    # two-head work-groups start at even channel tiles: none holds k and v, whose epilogues have different barriers
+    assert (w[w[:, 0] == 2, 1] % 2 == 0).all()
 
 
 @pytest.mark.parametrize("width", [192, 256])
