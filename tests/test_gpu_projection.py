@@ -38,8 +38,8 @@ def _check(cfg, got, ref, per_head):
     return eq, ek, ev
 
 
-# (config, c_in): token counts ragged against the token tile, reduction lengths of 1, 2, 3,
-# 5 and 7 steps of 64 (prologue only, tail only, steady loop once, steady loop + 4-step tail)
+# (config, c_in): token counts ragged against the token tile, reduction lengths of 1, 2, 3, 4, 5 and 7 steps of 64
+# (shorter than the rings of copies, as long, and with one steady step and more between the first and the last ones)
 SMALL = [
     (W.ChunkConfig("Q1", 31, 2, 4, 6, start_frame=5, n_frames=1, first_kv_frame=5), 256),
     (W.ChunkConfig("Q2", 32, 3, 5, 7, start_frame=6, n_frames=3, first_kv_frame=6), 64),
@@ -62,8 +62,8 @@ def test_small_every_element(P, cfg, c_in, per_head):
     _check(cfg, got, ref, per_head)
 
 
-# 40 heads are 120 channel tiles on 256 CUs: one or two rounds of either tile width, ragged in both; short
-# reductions, as above, take tiles of 256 tokens (checked in test_projection_widths.py, with those of 192).
+# 40 heads are 120 channel tiles on 256 CUs: one or two rounds of either tile width, ragged in both, in single heads and in
+# pairs; short reductions, as above, take tiles of 256 tokens (checked in test_projection_widths.py, with those of 192).
 @pytest.mark.parametrize("n,c_in", [(129, 320), (257, 64), (257, 448), (384, 128), (385, 320), (512, 192), (540, 192)])
 @pytest.mark.parametrize("per_head", [False, True], ids=["normHD", "normD"])
 def test_tile_widths(P, n, c_in, per_head):

@@ -1,6 +1,7 @@
-"""Which tile width the projection takes, and the 192-token tiles at their edges.  They are taken for
-reductions of more than 512 only, so of at least 9 steps: 9, 10 and 11 end the three-step loop in each of its
-ways.  The 256-token ones are what the short reductions of test_gpu_projection.py run."""
+"""Which tile width the projection takes, and the 192-token tiles at their edges.  Where both widths take the same rounds, as
+at most sizes here, they are taken for reductions of more than 512 only, so of at least 9 steps: the first step, steady ones
+and the last four (two with two heads per work-group), at an odd and an even number of them, so that W's and x's rings end at
+different places.  The 256-token ones are what the short reductions of test_gpu_projection.py run."""
 import numpy as np
 import pytest
 
@@ -20,10 +21,13 @@ def test_width_rule(n, heads, c_in, width):
     assert P.crope_qkv_project_tile_tokens(n, heads, c_in) == width
 
 
-# ragged against 192 by one row more and less, against the 96 tokens of a wave, one row alone, two tiles and three
+# Ragged against 192 by one row more and less, one row alone, two tiles and three; against the bodies of the last tile (64, 128, 192
+# tokens) and the 16, 32 and 48 tokens that a wave has in them with one head per work-group; the last one in pairs of heads
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,heads,c_in", [(1, 2, 576), (95, 3, 640), (97, 2, 704), (191, 2, 576), (192, 2, 640),
-                                          (193, 2, 704), (383, 5, 576), (385, 2, 640), (540, 40, 576)])
+                                          (193, 2, 704), (383, 5, 576), (385, 2, 640), (540, 40, 576),
+                                          (17, 2, 576), (63, 3, 640), (64, 2, 704), (65, 2, 576), (127, 3, 640), (128, 2, 704), (129, 2, 576),
+                                          (144, 2, 640), (145, 3, 704), (241, 2, 576), (320, 3, 640)])
 @pytest.mark.parametrize("per_head", [False, True], ids=["normHD", "normD"])
 @pytest.mark.parametrize("bias", [False, True], ids=["nobias", "bias"])
 def test_192_token_tiles(n, heads, c_in, per_head, bias):
