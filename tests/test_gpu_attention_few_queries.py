@@ -1,5 +1,5 @@
-"""Calls and last work-groups whose queries are one wave's (up to 32 of 128), which stores them without the other waves' way
-through LDS, and one query more: strided outputs, whole and split key ranges, with and without the log-sum-exp."""
+"""Calls and last work-groups of few queries, whose one or two waves store without the way through LDS that more take (up to 48 of
+128, 64 in a split key range), and one query more: strided outputs, whole and split key ranges, with and without the log-sum-exp."""
 import numpy as np
 import pytest
 
@@ -10,13 +10,13 @@ import harness as Hn
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("splits", [1, 3])
-@pytest.mark.parametrize("n_q", [1, 31, 32, 33, 129, 160, 161])
+@pytest.mark.parametrize("n_q", [1, 31, 32, 33, 48, 49, 64, 65, 129, 160, 161, 176, 177, 192, 193])
 @pytest.mark.parametrize("with_lse", [False, True], ids=["nolse", "lse"])
 def test_matches_the_oracle(n_q, splits, with_lse):
     import torch
     import oracle
     import paper_2603_06664_amd as P
-    print("lone wave: n_q %d splits %d lse %d" % (n_q, splits, with_lse), flush=True)
+    print("few queries: n_q %d splits %d lse %d" % (n_q, splits, with_lse), flush=True)
     H, n_keys, plan = 2, 201 * splits, (4, splits)
     rng = np.random.default_rng(n_q + 1000 * splits)
     q, k, v = (W.f32_to_bf16_bits(rng.standard_normal((n, H, 128)).astype(np.float32)) for n in (n_q, n_keys, n_keys))
