@@ -369,8 +369,9 @@ struct Wide {
   __device__ __forceinline__ float range_sum(int u) const { return denominator(u); }
 
   // As Narrow's; two MFMAs of 16 clocks stand where Narrow has one of 32.  The query tiles run forth under one fragment and
-  // back under the next, and the two key halves of a 32-channel step follow one another, so that every MFMA keeps one operand
-  // of the one before: the same products and sums for less power (480P last chunk 699 -> 691 us, rolling window 327 -> 324).
+  // back under the next, and the two key halves of a 32-channel step follow one another, so that an MFMA keeps one operand
+  // of the one before (all but the first of each half and the three that begin the scores' next 32 channels): the same products
+  // and sums for less power (the large cases 0.6 to 1.0 %: 480P last chunk 708 -> 702 us, rolling window 331 -> 328, 960p 10526 -> 10446).
   template <int PAR, bool DO_PV, bool DO_S, bool DO_SM, bool READ_V, bool MASK, bool FOLDED, bool SUM, class FEED>
   __device__ __forceinline__ void sub_iteration(int k_blk, int v_blk, int key0, const int (&lim)[kTiles], float c,
                                                 FEED& feed, int slot0, int k_flip, int v_shift) {

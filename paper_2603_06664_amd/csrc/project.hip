@@ -14,11 +14,12 @@
 // width when, and how many of which.  What bounds the loop is the way from the L2 to LDS: with all CUs copying it carries 24 TB/s (39 bytes per
 // clock and CU) in requests of 128 bytes and 13.5 TB/s in requests of 64, whatever the stride of the rows.  Hence two heads per
 // work-group (32 to 37 bytes per clock at full MFMA rate; one head 48 to 53), and reduction steps of 64, whose LDS
-// rows are one 128-byte request each (a version with steps of 32 and two work-groups per CU: 105 us where this takes 92).
+// rows are one 128-byte request each (a version with steps of 32 and two work-groups per CU, 4680 tokens x 12 heads, row-wide norm:
+// 105 us where this took 92).
 // Then latency: W and x have rings of their own in LDS, as deep as 160 KB allow (see Shape, half_step).
-// 4680 tokens x 12 heads, c_in 1536 92 -> 84 us (norm per head 72 -> 64), 585 x 40 heads, 5120 128 -> 109 (113 -> 94), 1320 x 16
-// heads, 2048 57 -> 49 (46 -> 37), 24 x 2 heads, 256 14.3 -> 8.3, against one head per work-group in 32x32x16 MFMAs with a three-stage
-// ring for both operands and the epilogue's tables and tile through LDS.
+// Row-wide norm (norm per head), us: 4680 tokens x 12 heads, c_in 1536, 91 -> 83 (72 -> 63), 585 x 40, 5120, 123 -> 98 (113 -> 90),
+// 1320 x 16, 2048, 56 -> 46 (46 -> 35), 24 x 2, 256, 14.0 -> 7.9 (10.2 -> 5.2), against one head per work-group in 32x32x16 MFMAs with a
+// three-stage ring for both operands and the epilogue's tables and tile through LDS.
 // LDS rows are 128 B; 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7), which makes the fragment reads (16 rows x
 // 16 B per quarter wave) conflict-free.
 //
@@ -169,7 +170,7 @@ constexpr int placed(int s, int n, int slots, int percent) {
 // The second half starts with the step's barrier (behind eight MFMAs, four with one head): nobody reads stage kt any more, and
 // stage kt+1 has landed.  Behind it stand the copies of x, in the first half those of W, in the first 60 % (x of two heads 45 %)
 // of the slots: with two heads x has about one step to land, and one that is requested later, or waited for
-// earlier, holds everybody up (585 rows x 40 heads: W two steps ahead in the second half, too, 107 us; W three and x two 96; W
+// earlier, holds everybody up (585 rows x 40 heads, norm per head: W two steps ahead in the second half, too, 107 us; W three and x two 96; W
 // moved to the first half and x requested early 94; barrier behind 0, 4, 8, 12 MFMAs 104, 94, 92, 93).
 template <class S, bool SECOND, bool STEADY>   // STEADY: 0 < kt and the copies of this step are known to exist
 __device__ __forceinline__ void half_step(f32x4_t (&acc)[4][S::TT], Frags<S::TT>& f, Frags<S::TT>& f_next, const TileLoader<S>& L,

@@ -13,8 +13,8 @@ constexpr int kTokGroup = 4;    // token tiles walked together with 8 pairs of h
 // stream through that XCD's L2 once; every XCD has a run of units.  With `doubles`, a unit is two neighbouring channel tiles; v
 // starts at an even one, so that no unit holds k and v, and the odd last one (odd numbers of heads) is one tile.  The first
 // `doubles` units of a run are one work-group's each, the others two's (of which the one for a missing tile leaves at once).
-// Without, a unit is one tile: units of two gave 4346 tokens x 5 heads, c_in 4608, 255 tiles, more than 256 work-groups and
-// so doubles, 99 us; 74 in one round.
+// Without, a unit is one tile: units of two gave 4346 tokens x 5 heads, c_in 4608, norm per head, 255 tiles, more than 256
+// work-groups and so doubles, 95 us; 71 in one round.
 struct ProjTiles {
   int ch_tiles, tok_tiles;
   int total, per_xcd, doubles;   // units
@@ -65,9 +65,9 @@ inline double project_span(int doubles, int singles) {
 }
 
 // Two heads per work-group or one.  Two are cheaper per row, one fills the chip more evenly: whole rounds of doubles
-// first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles:
-// 4680 tokens x 12 heads, 342 pairs on 256 CUs, 84 / 91 / 98; 585 x 40, one round of doubles 108 / 123 / 108; 600 x 12, one round
-// of singles 31 / 31 / 45).  An odd last tile is one tile, not two.  Equal estimates: as many whole rounds as possible, which move fewer
+// first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles, norm per head, then
+// row-wide: 4680 tokens x 12 heads, c_in 1536, 342 pairs on 256 CUs, 63 / 67 / 77, 82 / 87 / 98; 585 x 40, 5120, one round of doubles, 88 /
+// 102 / 87, 97 / 114 / 97; 600 x 12, 1536, one round of singles, 19 / 19 / 27, 26 / 26 / 36).  An odd last tile is one tile, not two.  Equal estimates: as many whole rounds as possible, which move fewer
 // bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33 units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads:
 // 0.2 % behind the fastest of all numbers of rounds on average, 11 % at worst; counted as two, it made that 1.5 and 43.
 inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
@@ -104,11 +104,15 @@ inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
   return pt;
 }
 
-// Two token widths of a tile.  256 moves fewer bytes per product (18720 tokens x 12 heads 306 us, 317 in tiles of 192);
-// 192 is taken where its rounds of one-head tiles over the 256 CUs, at 0.88 of the price, are fewer: calls whose rounds of
-// 256-wide tiles end nearly empty or whose last tile is mostly padding (us, 192 / 256: 585 x 40 heads 108 / 130; 4680 x 5
-// heads 94 / 111; 2340 x 12 46 / 51; but 1560 x 12 40 / 35; 3000 x 24 179 / 165; 1000 x 40 99 / 86).
-// At reductions of at most 512 the epilogue is most of a tile and 192 has to take fewer rounds at full price.
+// Two token widths of a tile.  256 moves fewer bytes per product (18720 tokens x 12 heads, row-wide norm, 306 us, 321 in tiles of
+// 192); 192 is taken where its rounds of one-head tiles over the 256 CUs, at 0.88 of the price, are fewer: calls whose rounds of
+// 256-wide tiles end nearly empty or that fit one round in either (us, 192 / 256, norm per head, then row-wide: 585 x 40 heads, c_in 5120,
+// 88 / 108, 97 / 115; 4680 x 5, 5120, 82 / 96, 93 / 106; 2340 x 12, 1536, 34 / 38, 46 / 51; 600 x 12, 1536, 19 / 22, 26 / 29; but 1560 x 12, 1536,
+// 29 / 25, 39 / 34; 3000 x 24, 3072, 153 / 141, 177 / 164; 1000 x 40, 2560, 83 / 66, 99 / 81).
+// At reductions of at most 512, 192 has to take fewer rounds at full price.  That line was fitted to a kernel with one head per
+// work-group throughout and the epilogue through LDS, and wants a new fit: with this one 192 is the faster at most short reductions (norm
+// per head: 200 x 2, 256, 8.3 / 9.5; 540 x 8, 512, 11.4 / 12.8; 4000 x 8, 512, 18.7 / 21.8; 540 x 40, 192, 14.3 / 17.1), though not at all of
+// them (8000 x 6, 384, 24.7 / 24.7, row-wide 42.9 / 40.1).
 constexpr double kMidCost = 0.88;
 constexpr int kShortReduction = 512;
 
