@@ -54,6 +54,12 @@ inline double project_span(int doubles, int singles) {
   const int late = doubles % kProjCusPerXcd;   // CUs that are a double behind the others
   double t0 = doubles / kProjCusPerXcd, t1 = t0 + 1.0, end = late ? t1 : t0;
   while (singles > 0) {
+    if (late && t0 > t1 && singles > 4 * kProjCusPerXcd) {   // from here on both kinds of CU take turns: whole turns at once
+      const int turns = singles / kProjCusPerXcd - 2;
+      singles -= turns * kProjCusPerXcd;
+      t0 += turns * kSingleCost;
+      t1 += turns * kSingleCost;
+    }
     double& t = late == 0 || t0 <= t1 ? t0 : t1;
     const int cus = &t == &t0 ? kProjCusPerXcd - late : late;
     const int waves = late == 0 ? (singles + cus - 1) / cus : 1;
@@ -67,8 +73,8 @@ inline double project_span(int doubles, int singles) {
 // Two heads per work-group or one.  Two are cheaper per row, one fills the chip more evenly: whole rounds of doubles
 // first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles, norm per head, then
 // row-wide: 4680 tokens x 12 heads, c_in 1536, 342 pairs on 256 CUs, 63 / 67 / 77, 82 / 87 / 98; 585 x 40, 5120, one round of doubles, 88 /
-// 102 / 87, 97 / 114 / 97; 600 x 12, 1536, one round of singles, 19 / 19 / 27, 26 / 26 / 36).  An odd last tile is one tile, not two.  Equal estimates: as many whole rounds as possible, which move fewer
-// bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33 units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads:
+// 102 / 87, 97 / 114 / 97; 600 x 12, 1536, one round of singles, 19 / 19 / 27, 26 / 26 / 36).  An odd last tile is one tile, not two.
+// Equal estimates: as many whole rounds as possible, which move fewer bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33 units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads:
 // 0.2 % behind the fastest of all numbers of rounds on average, 11 % at worst; counted as two, it made that 1.5 and 43.
 inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
   ProjTiles pt;
