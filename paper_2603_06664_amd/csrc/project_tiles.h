@@ -74,8 +74,9 @@ inline double project_span(int doubles, int singles) {
 // first, what is left in singles where that takes fewer rounds at 0.58 of a double's time (us, mixed / singles / doubles, norm per head, then
 // row-wide: 4680 tokens x 12 heads, c_in 1536, 342 pairs on 256 CUs, 63 / 67 / 77, 82 / 87 / 98; 585 x 40, 5120, one round of doubles, 88 /
 // 102 / 87, 97 / 114 / 97; 600 x 12, 1536, one round of singles, 19 / 19 / 27, 26 / 26 / 36).  An odd last tile is one tile, not two.
-// Equal estimates: as many whole rounds as possible, which move fewer bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33 units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads:
-// 0.2 % behind the fastest of all numbers of rounds on average, 11 % at worst; counted as two, it made that 1.5 and 43.
+// Equal estimates: as many whole rounds as possible, which move fewer bytes (6241 x 5, c_in 640, 24.5 us with 32 of an XCD's 33
+// units in doubles, 28.6 in singles).  340 sizes of odd numbers of heads: 0.2 % behind the fastest of all numbers of rounds on
+// average, 11 % at worst; 1.5 and 43 while the odd tile counted as two.
 inline ProjTiles make_tiles(int n_tokens, int n_heads, int tile_tokens) {
   ProjTiles pt;
   pt.ch_tiles = 3 * n_heads;
